@@ -50,19 +50,6 @@ __device__ inline void mma(const double *As, const double *Bs, int kpad, int row
     }
 }
 
-// storage index e of a k x k coupling matrix -> (nu, mu) (inverse of s_index, layouts 0 and 1)
-__device__ inline void s_coords(int swz, int k, int e, int &nu, int &mu) {
-    if (swz == 0) {
-        nu = e / k;
-        mu = e - nu * k;
-        return;
-    }
-    const int h = e & 1, lane = (e >> 1) & 63, rest = e >> 7, k8 = k >> 3;
-    const int kk2 = rest % k8, I = rest / k8;
-    nu = 16 * I + (lane & 15);
-    mu = 8 * kk2 + 4 * h + (lane >> 4);
-}
-
 template <int NJ>
 __global__ __launch_bounds__(256) void k_coupling_adj_mfma(int k, int swz, int64_t m, int32_t C,
                                                            const int64_t *__restrict__ cptr,

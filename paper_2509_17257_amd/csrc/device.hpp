@@ -67,8 +67,10 @@ struct DevMat {
     int64_t n_adm = 0, n_near = 0, near_entries = 0;
     h2x_prec storage = H2X_F64;
     int swz = 0;     // coupling-matrix layout (see s_index)
+    int64_t s_blk = 0;  // stored entries per coupling matrix (see s_block)
     int near_t = 0;  // near-field blocks stored transposed (|s| x |t| row-major)
     int mc = 0;      // every stage runs on the matrix cores (FP64, k = 64 or k <= 32)
+    int gk = 0;      // the same for the higher ranks (FP64, k = 125 to 512), products only
     int kernel = 0;
     int cplx = 0;                   // complex kernel: S and N hold a real and an imaginary plane
     int64_t s_plane = 0, n_plane = 0;  // elements per plane of S and N
@@ -120,8 +122,6 @@ struct DevMat {
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
 
 };
-
-inline int s_swizzled(const DevMat &dm) { return dm.swz; }
 
 // Work of clusters whose system has stopped can be left out of a product: flag
 // holds one entry per system (nonzero: stopped), sys_of the system of each

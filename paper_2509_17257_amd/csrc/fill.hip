@@ -164,13 +164,13 @@ __global__ void k_fill_E1(int32_t C, int p, const int32_t *__restrict__ parent, 
 template <typename T>
 __global__ void k_fill_S(int k, int kernel, double ell, double npts, const int32_t *__restrict__ adm_row,
                          const int32_t *__restrict__ adm_col, const double *__restrict__ nodes,
-                         T *__restrict__ S, int swz, int64_t s_plane) {
+                         T *__restrict__ S, int swz, int64_t s_blk, int64_t s_plane) {
     const int64_t b = blockIdx.x;
     const int32_t t = adm_row[b], s = adm_col[b];
     for (int e = threadIdx.x; e < k * k; e += blockDim.x) {
         const int nu = e / k, mu = e % k;
         const double *xa = &nodes[((int64_t)t * k + nu) * 3], *xb = &nodes[((int64_t)s * k + mu) * 3];
-        const int64_t at = b * k * k + s_index(swz, k, nu, mu);
+        const int64_t at = b * s_blk + s_index(swz, k, nu, mu);
         if (kernel == H2X_KERNEL_HELMHOLTZ) {
             double re, im;
             kernel_gc(ell, npts, xa, xb, re, im);
@@ -180,6 +180,12 @@ __global__ void k_fill_S(int k, int kernel, double ell, double npts, const int32
             S[at] = from_double<T>(kernel_g(kernel, ell, xa, xb));
         }
     }
+    if (s_blk > k * k)  // the padding of layout 1
+        for (int e = threadIdx.x; e < s_blk; e += blockDim.x) {
+            int nu, mu;
+            s_coords(swz, k, e, nu, mu);
+            if (nu >= k || mu >= k) S[b * s_blk + e] = from_double<T>(0.0);
+        }
 }
 
 // N_(t,s)[i, j] = g(x_i, x_j) + shift [i == j], row-major |t| x |s|, or stored
@@ -233,7 +239,7 @@ hipError_t fill_SN(const DevMat &dm, hipStream_t st) {
         const double npts = (double)(P.sys_row[i + 1] - P.sys_row[i]);  // points of system i
         if (na > 0)
             hipLaunchKernelGGL(k_fill_S<T>, dim3((unsigned)na), dim3(256), 0, st, dm.k, kernel, ell, npts,
-                               dm.adm_row + a, dm.adm_col + a, dm.nodes, (T *)dm.S + a * dm.k * dm.k, s_swizzled(dm),
+                               dm.adm_row + a, dm.adm_col + a, dm.nodes, (T *)dm.S + a * dm.s_blk, dm.swz, dm.s_blk,
                                dm.s_plane);
         if (nq > 0)
             hipLaunchKernelGGL(k_fill_N<TN>, dim3((unsigned)nq), dim3(256), 0, st, kernel, ell, shift, npts,
@@ -285,11 +291,14 @@ size_t mat_layout(const Plan &P, h2x_prec storage, DevMat *dm, char *base) {
     d.leaf_half = P.leaf_half;
     d.n_adm = na; d.n_near = nn; d.near_entries = P.near_entries; d.storage = storage;
     d.kernel = P.prm.kernel; d.ell = P.prm.ell; d.shift = P.prm.shift; d.plan = &P;
-    d.swz = k != 64 ? 0 : (storage == H2X_F64 ? 1 : (storage == H2X_F32 ? 2 : 3));
+    // higher ranks of the FP64 operator (p = 5 to 8): their own matrix-core kernels
+    d.gk = (storage == H2X_F64 && k > 64) ? 1 : 0;
+    d.swz = d.gk ? 1 : (k != 64 ? 0 : (storage == H2X_F64 ? 1 : (storage == H2X_F32 ? 2 : 3)));
+    d.s_blk = s_block(d.swz, k);
     // matrix-core layout (transposed near field, transposed leaf bases): FP64, k = 64 or k <= 32
     d.mc = (storage == H2X_F64 && (k == 64 || k <= 32)) ? 1 : 0;
     // low-precision operators with k = 64 use the same transposed near field (FP32) and leaf bases
-    d.near_t = (d.mc || (storage != H2X_F64 && (k == 64 || k <= 32))) ? 1 : 0;
+    d.near_t = (d.mc || d.gk || (storage != H2X_F64 && (k == 64 || k <= 32))) ? 1 : 0;
     d.first = carve<int32_t>(cur, base, C);
     d.size = carve<int32_t>(cur, base, C);
     d.parent = carve<int32_t>(cur, base, C);
@@ -337,7 +346,7 @@ size_t mat_layout(const Plan &P, h2x_prec storage, DevMat *dm, char *base) {
     const int64_t nstored = d.near_t ? P.near_entries_t : P.near_entries;
     d.s_plane = d.cplx ? na * k * k : 0;
     d.n_plane = d.cplx ? nstored : 0;
-    d.S = carve<char>(cur, base, es * planes * (size_t)(na ? na : 1) * k * k);
+    d.S = carve<char>(cur, base, es * planes * (size_t)(na ? na : 1) * d.s_blk);
     d.N = carve<char>(cur, base, ens * planes * (size_t)(nstored ? nstored : 1) + 16);
     d.Vt = d.near_t ? carve<char>(cur, base, es * (size_t)P.vt_entries) : nullptr;
     if (dm) *dm = d;

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void k_coupling_adj(int k, int64_t m, const in
         for (int64_t q = cptr[s]; q < cptr[s + 1]; ++q) {
             const int64_t b = cblk[q];
             const int32_t t = adm_row[b];
-            const double *Sb = S + b * k * k;
+            const double *Sb = S + b * s_block(swz, k);
             for (int u0 = 0; u0 < k; u0 += TR) {
                 const int uc = min(TR, k - u0);
                 // As[mu][nu] = S_b[nu][mu]
@@ -307,12 +307,12 @@ __global__ void k_gather_even(int64_t n, int64_t m, const int64_t *__restrict__ 
 // coupling matrices read back row-major (undoing the matrix-core layout)
 __global__ void k_read_S(int k, int swz, const double *__restrict__ S, double *__restrict__ out) {
     const int64_t b = blockIdx.x, kk = (int64_t)k * k;
-    for (int e = threadIdx.x; e < kk; e += blockDim.x) out[b * kk + e] = S[b * kk + s_index(swz, k, e / k, e % k)];
+    for (int e = threadIdx.x; e < kk; e += blockDim.x) out[b * kk + e] = S[b * s_block(swz, k) + s_index(swz, k, e / k, e % k)];
 }
 
 __global__ void k_write_S(int k, int swz, const double *__restrict__ in, double *__restrict__ S) {
     const int64_t b = blockIdx.x, kk = (int64_t)k * k;
-    for (int e = threadIdx.x; e < kk; e += blockDim.x) S[b * kk + s_index(swz, k, e / k, e % k)] = in[b * kk + e];
+    for (int e = threadIdx.x; e < kk; e += blockDim.x) S[b * s_block(swz, k) + s_index(swz, k, e / k, e % k)] = in[b * kk + e];
 }
 
 int64_t even(int64_t m) { return m + (m & 1); }

@@ -16,6 +16,7 @@
 
 #include "device.hpp"
 #include "coupling_lp.hpp"
+#include "coupling_rows.hpp"
 #include "leaf_cat.hpp"
 #include "leaf_cat_lp.hpp"
 #include "leaf_lp.hpp"
@@ -523,9 +524,9 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     };
     // complex operator: y-hat += S_im (J x-hat), so that y-hat = (S_re + i S_im) x-hat per complex column
     auto coupling = [&](hipStream_t s, int32_t nrows, const int32_t *rows, size_t keep) {
-        launch_coupling_fast<double, double>(dm, m, xh, yh, ldh, s, sk, cfg.nj_coupling, 0, nrows, rows, keep);
+        launch_coupling_fast(dm, m, xh, yh, ldh, s, sk, cfg.nj_coupling, 0, nrows, rows, keep);
         if (dm.cplx)
-            launch_coupling_fast<double, double>(dm, m, xh, yh, ldh, s, sk, cfg.nj_coupling, 1, nrows, rows, keep);
+            launch_coupling_fast(dm, m, xh, yh, ldh, s, sk, cfg.nj_coupling, 1, nrows, rows, keep);
     };
     const int dlo = std::max(1, P.adm_depth + 1);
     if (halves) {
@@ -638,60 +639,173 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     if (ev) (void)hipEventRecord(ev[6], st);
 }
 
+// Transfer levels and forward leaf transform of the ranks above 64 (p = 5 to 8): 16-column slabs
+// (the Kronecker passes hold both sons' k rows in LDS: 139 KB at p = 8)
+void gen_up_levels(const DevMat &dm, int64_t m, double *xh, int64_t ldh, hipStream_t st, Skip sk) {
+    const Plan &P = *dm.plan;
+    for (int d = dm.depth_max - 1; d >= P.adm_depth; --d) {
+        const int32_t b = P.lvl_inner_ptr[d], e = P.lvl_inner_ptr[d + 1];
+        if (e <= b) continue;
+        auto go = [&](auto Pc) {
+            hipLaunchKernelGGL((kron::k_up<decltype(Pc)::value, 16>), dim3(e - b, (unsigned)((m + 15) / 16)), dim3(256),
+                               0, st, m, dm.lvl_inner + b, dm.up_son + 2 * b, dm.E1, xh, ldh, sk);
+        };
+        switch (dm.p) {
+            case 5: go(std::integral_constant<int, 5>{}); break;
+            case 6: go(std::integral_constant<int, 6>{}); break;
+            case 7: go(std::integral_constant<int, 7>{}); break;
+            default: go(std::integral_constant<int, 8>{}); break;
+        }
+    }
+}
+
+void gen_down_levels(const DevMat &dm, int64_t m, double *yh, int64_t ldh, hipStream_t st, Skip sk) {
+    const Plan &P = *dm.plan;
+    for (int d = std::max(1, P.adm_depth + 1); d <= dm.depth_max; ++d) {
+        const int32_t b = P.lvl_ptr[d], e = P.lvl_ptr[d + 1];
+        if (e <= b) continue;
+        auto go = [&](auto Pc) {
+            hipLaunchKernelGGL((kron::k_down<decltype(Pc)::value, 16>), dim3(e - b, (unsigned)((m + 15) / 16)),
+                               dim3(256), 0, st, m, dm.lvl_all + b, dm.dn_par + b, dm.E1, yh, ldh, sk);
+        };
+        switch (dm.p) {
+            case 5: go(std::integral_constant<int, 5>{}); break;
+            case 6: go(std::integral_constant<int, 6>{}); break;
+            case 7: go(std::integral_constant<int, 7>{}); break;
+            default: go(std::integral_constant<int, 8>{}); break;
+        }
+    }
+}
+
+void gen_fwd_leaf(const DevMat &dm, int64_t m, const double *Xt, int64_t ldxt, double *xh, int64_t ldh, hipStream_t st,
+                  Skip sk) {
+    const int nj = (int)std::min<int64_t>(4, (m + 15) / 16);
+    const dim3 grid(dm.L, (unsigned)((m + 16 * nj - 1) / (16 * nj)), (unsigned)((dm.k + 63) / 64));
+    auto go = [&](auto NJc) {
+        hipLaunchKernelGGL(mfma::k_fwd_leaf_rows<decltype(NJc)::value>, grid, dim3(256), 0, st, dm.k, m, dm.leaves,
+                           dm.first, dm.size, (const double *)dm.V, Xt, ldxt, xh, ldh, sk);
+    };
+    switch (nj) {
+        case 1: go(std::integral_constant<int, 1>{}); break;
+        case 2: go(std::integral_constant<int, 2>{}); break;
+        case 3: go(std::integral_constant<int, 3>{}); break;
+        default: go(std::integral_constant<int, 4>{}); break;
+    }
+}
+
+// X in tree order with an even leading dimension and 16-byte alignment: X itself, or its copy in xt_ws
+const double *tree_rows(const DevMat &dm, int64_t m, const double *X, int64_t &ldx, bool tree_order, double *xt_ws,
+                        hipStream_t st) {
+    if (tree_order && !(ldx & 1) && !((uintptr_t)X & 15)) return X;
+    const int64_t ldxt = even_ld(m), cnt = dm.n * ldxt;
+    hipLaunchKernelGGL(mfma::k_gather, dim3((unsigned)((cnt / 2 + 255) / 256)), dim3(256), 0, st, dm.n, m,
+                       tree_order ? nullptr : dm.perm, X, ldx, xt_ws, ldxt);
+    ldx = ldxt;
+    return xt_ws;
+}
+
+// All five stages of the FP64 operators of rank above 64 on the matrix cores.
+void matmul_gen_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alpha, const double *X, int64_t ldx,
+                    double beta, double *Y, int64_t ldy, int to, double *xh, double *yh, int64_t ldh, double *xt_ws,
+                    hipStream_t st, const std::function<void(int)> &mark, hipEvent_t *ev, const int32_t *skip) {
+    const Skip sk{skip, dm.sys_of};
+    mark(0);
+    int64_t ldxt = ldx;
+    const double *Xt = tree_rows(dm, m, X, ldxt, to, xt_ws, st);
+    gen_fwd_leaf(dm, m, Xt, ldxt, xh, ldh, st, sk);
+    mark(1);
+    gen_up_levels(dm, m, xh, ldh, st, sk);
+    mark(2);
+    launch_coupling_rows(dm, m, xh, yh, ldh, st, sk);
+    mark(3);
+    gen_down_levels(dm, m, yh, ldh, st, sk);
+    mark(4);
+    const int NP = cfg.np_leaf ? cfg.np_leaf : (m > 32 ? 2 : 1);
+    const size_t cat_lds = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
+    const unsigned gl = (unsigned)((m + 32 * NP - 1) / (32 * NP));
+    // one contraction per leaf where its table of near rows fits in LDS (and X in 32-bit byte
+    // offsets), else the generic tiles
+    if (cat_lds + sizeof(double) * 64 * (32 * NP + 1) + 64 <= 65536 &&
+        sizeof(double) * (size_t)dm.n * (size_t)ldxt < ((size_t)1 << 32)) {
+        const int64_t slots = (int64_t)8 * ((dm.L + 7) / 8) * gl;
+        const mfma::LeafCatArgs a{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm,
+                                  (const double *)dm.Vt, dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off,
+                                  (const double *)dm.N, Xt, ldxt, alpha, beta, Y, ldy, to, 1, 1, sk};
+        if (NP == 2)
+            hipLaunchKernelGGL(mfma::k_leaf_cat<2>, dim3((unsigned)slots), dim3(256), cat_lds, st, a, (int64_t)0, slots);
+        else
+            hipLaunchKernelGGL(mfma::k_leaf_cat<1>, dim3((unsigned)slots), dim3(256), cat_lds, st, a, (int64_t)0, slots);
+    } else {
+        hipLaunchKernelGGL((k_leaf_near<double, double, double>), dim3(dm.L, (unsigned)((m + TC - 1) / TC)), dim3(256), 0,
+                           st, dm.k, m, dm.leaves, dm.first, dm.size, dm.perm, (const double *)dm.V, yh, ldh,
+                           dm.near_ptr, dm.near_col, dm.near_off, (const double *)dm.N, X, ldx, alpha, beta, Y, ldy, to,
+                           dm.near_t);
+    }
+    mark(5);
+    if (ev) (void)hipEventRecord(ev[6], st);
+}
+
 template <typename Acc>
 size_t hat_bytes(const DevMat &dm, int64_t m) {
     return align_up(sizeof(Acc) * (size_t)dm.C * dm.k * (size_t)even_ld(m));
 }
 
-template <typename T, typename TN, typename Acc>
-hipError_t matmul_typed(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alpha, const double *X, int64_t ldx,
-                        double beta, double *Y, int64_t ldy, bool tree_order, char *ws, hipStream_t st, hipEvent_t *ev,
-                        const int32_t *skip) {
+// FP64 operators: k = 64 or k <= 32 (mc), or the higher ranks (gk)
+hipError_t matmul_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alpha, const double *X, int64_t ldx,
+                      double beta, double *Y, int64_t ldy, bool tree_order, char *ws, hipStream_t st, hipEvent_t *ev,
+                      const int32_t *skip) {
+    const std::function<void(int)> mk = [&](int i) {
+        if (ev) (void)hipEventRecord(ev[i], st);
+    };
+    const int64_t ldh = even_ld(m);
+    const int to = tree_order ? 1 : 0;
+    double *xh = (double *)ws, *yh = (double *)(ws + hat_bytes<double>(dm, m));
+    double *xt = (double *)(ws + 2 * hat_bytes<double>(dm, m));
+    if (dm.gk) {
+        matmul_gen_f64(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, to, xh, yh, ldh, xt, st, mk, ev, skip);
+        return hipGetLastError();
+    }
+    switch (cfg.nj_transfer ? (int)cfg.nj_transfer : (int)std::min<int64_t>(4, (m + 15) / 16)) {
+        case 1: matmul_mfma_f64<1>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, to, xh, yh, ldh, xt, st, mk, ev, skip); break;
+        case 2: matmul_mfma_f64<2>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, to, xh, yh, ldh, xt, st, mk, ev, skip); break;
+        case 3: matmul_mfma_f64<3>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, to, xh, yh, ldh, xt, st, mk, ev, skip); break;
+        default: matmul_mfma_f64<4>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, to, xh, yh, ldh, xt, st, mk, ev, skip); break;
+    }
+    return hipGetLastError();
+}
+
+// FP32 and BF16 operators (near field FP32, FP32 accumulation)
+template <typename T>
+hipError_t matmul_lp(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alpha, const double *X, int64_t ldx,
+                     double beta, double *Y, int64_t ldy, bool tree_order, char *ws, hipStream_t st, hipEvent_t *ev,
+                     const int32_t *skip) {
+    typedef float TN;
+    typedef float Acc;
     auto mark = [&](int i) {
         if (ev) (void)hipEventRecord(ev[i], st);
     };
     const Plan &P = *dm.plan;
-    // low-precision operator in the matrix-core layout (k = 64 or k <= 32): FP32
-    // matrix-core coupling and leaf stage, generic transfer passes
-    const bool lpmc = !std::is_same<T, double>::value && dm.near_t && (dm.k == 64 || dm.k <= 32);
-    const int64_t ldh = (dm.mc || lpmc) ? even_ld(m) : m;
+    // matrix-core layout (k = 64 or k <= 32): FP32 matrix-core coupling and leaf stage,
+    // generic kernels else
+    const bool lpmc = dm.near_t && (dm.k == 64 || dm.k <= 32);
+    const int64_t ldh = lpmc ? even_ld(m) : m;
     Acc *xh = (Acc *)ws;
     Acc *yh = (Acc *)(ws + hat_bytes<Acc>(dm, m));
     const unsigned gy = (unsigned)((m + TC - 1) / TC);
     const int to = tree_order ? 1 : 0;
     const T *V = (const T *)dm.V, *E = (const T *)dm.E, *S = (const T *)dm.S;
-    (void)skip;  // only the matrix-core path leaves stopped systems out
-
-    if constexpr (std::is_same<T, double>::value && std::is_same<Acc, double>::value) {
-        if (dm.mc) {
-            const std::function<void(int)> mk = mark;
-            double *xt = (double *)(ws + 2 * hat_bytes<Acc>(dm, m));
-            switch (cfg.nj_transfer ? (int)cfg.nj_transfer : (int)std::min<int64_t>(4, (m + 15) / 16)) {
-                case 1: matmul_mfma_f64<1>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, to, xh, yh, ldh, xt, st, mk, ev, skip); break;
-                case 2: matmul_mfma_f64<2>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, to, xh, yh, ldh, xt, st, mk, ev, skip); break;
-                case 3: matmul_mfma_f64<3>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, to, xh, yh, ldh, xt, st, mk, ev, skip); break;
-                default: matmul_mfma_f64<4>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, to, xh, yh, ldh, xt, st, mk, ev, skip); break;
-            }
-            return hipGetLastError();
-        }
-    }
 
     mark(0);
-    bool fwd_done = false;
-    if constexpr (std::is_same<Acc, float>::value && !std::is_same<T, double>::value) {
-        if (lpmc) {
-            // the FP32 tree-ordered copy of X serves the forward leaf transform and the leaf stage
-            float *xt = (float *)(ws + 2 * hat_bytes<Acc>(dm, m));
-            const int64_t ldxt = even_ld(m);
-            hipLaunchKernelGGL(lp::k_gather_f32, dim3((unsigned)((dm.n + 3) / 4)), dim3(256), 0, st, dm.n, m,
-                               to ? nullptr : dm.perm, X, ldx, xt, ldxt);
-            if (dm.L > 0)
-                hipLaunchKernelGGL((tlp::k_fwd_leaf_lp<T>), dim3(dm.L, gy), dim3(256), 0, st, dm.k, m, dm.leaves,
-                                   dm.first, dm.size, V, (const float *)xt, ldxt, xh, ldh);
-            fwd_done = true;
-        }
-    }
-    if (!fwd_done)
+    if (lpmc) {
+        // the FP32 tree-ordered copy of X serves the forward leaf transform and the leaf stage
+        float *xt = (float *)(ws + 2 * hat_bytes<Acc>(dm, m));
+        const int64_t ldxt = even_ld(m);
+        hipLaunchKernelGGL(lp::k_gather_f32, dim3((unsigned)((dm.n + 3) / 4)), dim3(256), 0, st, dm.n, m,
+                           to ? nullptr : dm.perm, X, ldx, xt, ldxt);
+        if (dm.L > 0)
+            hipLaunchKernelGGL((tlp::k_fwd_leaf_lp<T>), dim3(dm.L, gy), dim3(256), 0, st, dm.k, m, dm.leaves,
+                               dm.first, dm.size, V, (const float *)xt, ldxt, xh, ldh);
+    } else
         hipLaunchKernelGGL((k_fwd_leaf<T, Acc>), dim3(dm.L, gy), dim3(256), 0, st, dm.k, m, dm.leaves, dm.first,
                            dm.size, dm.perm, V, X, ldx, to, xh, ldh);
     mark(1);
@@ -702,101 +816,90 @@ hipError_t matmul_typed(const DevMat &dm, const TuneCfg &cfg, int64_t m, double 
     // that way, 0.20 -> 0.23 ms, and keeps 32)
     const unsigned g64 = (unsigned)((m + 63) / 64);
     auto up_lp = [&](int32_t b, int32_t e) {
-        if constexpr (std::is_same<Acc, float>::value && !std::is_same<T, double>::value) {
-            if (dm.k == 64)
-                hipLaunchKernelGGL((tlp::k_up_lp<16, T>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m,
-                                   dm.lvl_inner + b, dm.son0, dm.son1, E, xh, ldh);
-            else
-                hipLaunchKernelGGL((tlp::k_up_lp<8, T>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m,
-                                   dm.lvl_inner + b, dm.son0, dm.son1, E, xh, ldh);
-            return true;
-        }
-        return false;
+        if (dm.k == 64)
+            hipLaunchKernelGGL((tlp::k_up_lp<16, T>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_inner + b,
+                               dm.son0, dm.son1, E, xh, ldh);
+        else
+            hipLaunchKernelGGL((tlp::k_up_lp<8, T>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_inner + b,
+                               dm.son0, dm.son1, E, xh, ldh);
     };
     auto down_lp = [&](int32_t b, int32_t e) {
-        if constexpr (std::is_same<Acc, float>::value && !std::is_same<T, double>::value) {
-            if (dm.k == 64 && m > 32)
-                hipLaunchKernelGGL((tlp::k_down_lp<16, T, 4>), dim3(e - b, g64), dim3(256), 0, st, dm.k, m,
-                                   dm.lvl_all + b, dm.parent, E, yh, ldh);
-            else if (dm.k == 64)
-                hipLaunchKernelGGL((tlp::k_down_lp<16, T>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m,
-                                   dm.lvl_all + b, dm.parent, E, yh, ldh);
-            else
-                hipLaunchKernelGGL((tlp::k_down_lp<8, T>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m,
-                                   dm.lvl_all + b, dm.parent, E, yh, ldh);
-            return true;
-        }
-        return false;
+        if (dm.k == 64 && m > 32)
+            hipLaunchKernelGGL((tlp::k_down_lp<16, T, 4>), dim3(e - b, g64), dim3(256), 0, st, dm.k, m,
+                               dm.lvl_all + b, dm.parent, E, yh, ldh);
+        else if (dm.k == 64)
+            hipLaunchKernelGGL((tlp::k_down_lp<16, T>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_all + b,
+                               dm.parent, E, yh, ldh);
+        else
+            hipLaunchKernelGGL((tlp::k_down_lp<8, T>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_all + b,
+                               dm.parent, E, yh, ldh);
     };
     for (int d = dm.depth_max - 1; d >= P.adm_depth; --d) {
         const int32_t b = P.lvl_inner_ptr[d], e = P.lvl_inner_ptr[d + 1];
-        if (e > b && !(lpmc && up_lp(b, e)))
+        if (e > b && lpmc)
+            up_lp(b, e);
+        else if (e > b)
             hipLaunchKernelGGL((k_up<T, Acc>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_inner + b, dm.son0,
                                dm.son1, E, xh, ldh);
     }
     mark(2);
-    bool fast = launch_coupling_fast<T, Acc>(dm, m, xh, yh, ldh, st, Skip{}, 0);
-    if constexpr (std::is_same<Acc, float>::value && !std::is_same<T, double>::value)
-        if (!fast) {
-            // BF16, k = 64: x-hat rounded to BF16 once per cluster for the coupling
-            uint16_t *xb = nullptr;
-            if (std::is_same<T, bf16_t>::value && lpmc && dm.k == 64) {
-                xb = (uint16_t *)(ws + 2 * hat_bytes<Acc>(dm, m) + align_up(sizeof(float) * (size_t)dm.n * even_ld(m)));
-                const int64_t cnt4 = (int64_t)dm.C * dm.k * ldh / 4;  // k = 64: a multiple of 4
-                hipLaunchKernelGGL(k_pack_bf16, dim3((unsigned)((cnt4 + 255) / 256)), dim3(256), 0, st, cnt4,
-                                   (const float4 *)xh, (uint2 *)xb);
-            }
-            fast = launch_coupling_lp<T>(dm, m, xh, xb, yh, ldh, st, Skip{skip, dm.sys_of}, cfg.nj_coupling);
-        }
-    if (!fast)
+    // BF16, k = 64: x-hat rounded to BF16 once per cluster for the coupling
+    uint16_t *xb = nullptr;
+    if (std::is_same<T, bf16_t>::value && lpmc && dm.k == 64) {
+        xb = (uint16_t *)(ws + 2 * hat_bytes<Acc>(dm, m) + align_up(sizeof(float) * (size_t)dm.n * even_ld(m)));
+        const int64_t cnt4 = (int64_t)dm.C * dm.k * ldh / 4;  // k = 64: a multiple of 4
+        hipLaunchKernelGGL(k_pack_bf16, dim3((unsigned)((cnt4 + 255) / 256)), dim3(256), 0, st, cnt4,
+                           (const float4 *)xh, (uint2 *)xb);
+    }
+    if (!launch_coupling_lp<T>(dm, m, xh, xb, yh, ldh, st, Skip{skip, dm.sys_of}, cfg.nj_coupling))
         hipLaunchKernelGGL((k_coupling<T, Acc>), dim3(dm.C, gy), dim3(256), 0, st, dm.k, m, dm.adm_ptr, dm.adm_col, S,
                            dm.swz, xh, yh, ldh);
     mark(3);
     for (int d = std::max(1, P.adm_depth + 1); d <= dm.depth_max; ++d) {
         const int32_t b = P.lvl_ptr[d], e = P.lvl_ptr[d + 1];
-        if (e > b && !(lpmc && down_lp(b, e)))
+        if (e > b && lpmc)
+            down_lp(b, e);
+        else if (e > b)
             hipLaunchKernelGGL((k_down<T, Acc>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_all + b, dm.parent,
                                E, yh, ldh);
     }
     mark(4);
-    if constexpr (std::is_same<Acc, float>::value && !std::is_same<T, double>::value && std::is_same<TN, float>::value) {
-        if (lpmc) {
-            float *xt = (float *)(ws + 2 * hat_bytes<Acc>(dm, m));  // gathered before the forward transform
-            const int64_t ldxt = even_ld(m);
-            const Skip sk{skip, dm.sys_of};
-            const int rb = std::is_same<T, bf16_t>::value ? 1 : 0;
-            const unsigned gl8 = 8 * ((dm.L + 7) / 8);
-            const int NPl = cfg.np_leaf ? cfg.np_leaf : (m > 32 ? 2 : 1);
-            // one contraction per leaf (built-in where its table of near rows fits in LDS;
-            // leaf_kind 3 or 0), else a 64-row tile per wave and term (leaf_kind 1 or 2)
-            const size_t cat_lds = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
-            const size_t red = NPl == 2 ? lp::leaf_cat_lp_red_bytes<2>() : lp::leaf_cat_lp_red_bytes<1>();
-            // (it reads the rows of X through a buffer resource: 32-bit byte offsets)
-            const bool cat_ok = !dm.cplx && cat_lds + red + 64 <= 65536 &&
-                                sizeof(float) * (size_t)dm.n * (size_t)ldxt < ((size_t)1 << 32);
-            if (cat_ok && (cfg.leaf_kind == 0 || cfg.leaf_kind == 3)) {
-                const lp::LeafCatLpArgs a{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm,
-                                          dm.Vt, dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off,
-                                          (const float *)dm.N, xt, ldxt, alpha, beta, Y, ldy, to, rb, sk};
-                const unsigned grid = gl8 * (unsigned)((m + 32 * NPl - 1) / (32 * NPl));
-                if (NPl == 2)
-                    hipLaunchKernelGGL((lp::k_leaf_cat_lp<2, T>), dim3(grid), dim3(256), cat_lds, st, a);
-                else
-                    hipLaunchKernelGGL((lp::k_leaf_cat_lp<1, T>), dim3(grid), dim3(256), cat_lds, st, a);
-            } else if (NPl == 2)
-                hipLaunchKernelGGL((lp::k_leaf_lp<2, T>), dim3(gl8 * (unsigned)((m + 63) / 64)), dim3(256), 0, st,
-                                   dm.k, m, dm.L, dm.leaves, dm.first, dm.size, dm.perm, (const T *)dm.Vt, dm.vt_off,
-                                   yh, ldh, dm.near_ptr, dm.near_col, dm.near_off, (const float *)dm.N, xt, ldxt,
-                                   alpha, beta, Y, ldy, to, rb, sk);
+    if (lpmc) {
+        float *xt = (float *)(ws + 2 * hat_bytes<Acc>(dm, m));  // gathered before the forward transform
+        const int64_t ldxt = even_ld(m);
+        const Skip sk{skip, dm.sys_of};
+        const int rb = std::is_same<T, bf16_t>::value ? 1 : 0;
+        const unsigned gl8 = 8 * ((dm.L + 7) / 8);
+        const int NPl = cfg.np_leaf ? cfg.np_leaf : (m > 32 ? 2 : 1);
+        // one contraction per leaf (built-in where its table of near rows fits in LDS;
+        // leaf_kind 3 or 0), else a 64-row tile per wave and term (leaf_kind 1 or 2)
+        const size_t cat_lds = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
+        const size_t red = NPl == 2 ? lp::leaf_cat_lp_red_bytes<2>() : lp::leaf_cat_lp_red_bytes<1>();
+        // (it reads the rows of X through a buffer resource: 32-bit byte offsets)
+        const bool cat_ok = !dm.cplx && cat_lds + red + 64 <= 65536 &&
+                            sizeof(float) * (size_t)dm.n * (size_t)ldxt < ((size_t)1 << 32);
+        if (cat_ok && (cfg.leaf_kind == 0 || cfg.leaf_kind == 3)) {
+            const lp::LeafCatLpArgs a{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm,
+                                      dm.Vt, dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off,
+                                      (const float *)dm.N, xt, ldxt, alpha, beta, Y, ldy, to, rb, sk};
+            const unsigned grid = gl8 * (unsigned)((m + 32 * NPl - 1) / (32 * NPl));
+            if (NPl == 2)
+                hipLaunchKernelGGL((lp::k_leaf_cat_lp<2, T>), dim3(grid), dim3(256), cat_lds, st, a);
             else
-                hipLaunchKernelGGL((lp::k_leaf_lp<1, T>), dim3(gl8 * (unsigned)((m + 31) / 32)), dim3(256), 0, st,
-                                   dm.k, m, dm.L, dm.leaves, dm.first, dm.size, dm.perm, (const T *)dm.Vt, dm.vt_off,
-                                   yh, ldh, dm.near_ptr, dm.near_col, dm.near_off, (const float *)dm.N, xt, ldxt,
-                                   alpha, beta, Y, ldy, to, rb, sk);
-            mark(5);
-            if (ev) (void)hipEventRecord(ev[6], st);
-            return hipGetLastError();
-        }
+                hipLaunchKernelGGL((lp::k_leaf_cat_lp<1, T>), dim3(grid), dim3(256), cat_lds, st, a);
+        } else if (NPl == 2)
+            hipLaunchKernelGGL((lp::k_leaf_lp<2, T>), dim3(gl8 * (unsigned)((m + 63) / 64)), dim3(256), 0, st,
+                               dm.k, m, dm.L, dm.leaves, dm.first, dm.size, dm.perm, (const T *)dm.Vt, dm.vt_off,
+                               yh, ldh, dm.near_ptr, dm.near_col, dm.near_off, (const float *)dm.N, xt, ldxt,
+                               alpha, beta, Y, ldy, to, rb, sk);
+        else
+            hipLaunchKernelGGL((lp::k_leaf_lp<1, T>), dim3(gl8 * (unsigned)((m + 31) / 32)), dim3(256), 0, st,
+                               dm.k, m, dm.L, dm.leaves, dm.first, dm.size, dm.perm, (const T *)dm.Vt, dm.vt_off,
+                               yh, ldh, dm.near_ptr, dm.near_col, dm.near_off, (const float *)dm.N, xt, ldxt,
+                               alpha, beta, Y, ldy, to, rb, sk);
+        mark(5);
+        if (ev) (void)hipEventRecord(ev[6], st);
+        return hipGetLastError();
     }
     hipLaunchKernelGGL((k_leaf_near<T, TN, Acc>), dim3(dm.L, gy), dim3(256), 0, st, dm.k, m, dm.leaves, dm.first,
                        dm.size, dm.perm, V, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off, (const TN *)dm.N, X, ldx,
@@ -849,16 +952,7 @@ hipError_t run_forward_transform(const DevMat &dm, int64_t m, const double *X, i
         }
         return hipGetLastError();
     }
-    const unsigned gy = (unsigned)((m + TC - 1) / TC);
-    hipLaunchKernelGGL((k_fwd_leaf<double, double>), dim3(dm.L, gy), dim3(256), 0, st, dm.k, m, dm.leaves, dm.first,
-                       dm.size, dm.perm, V, X, ldx, tree_order ? 1 : 0, xh, ldh);
-    for (int d = dm.depth_max - 1; d >= P.adm_depth; --d) {
-        const int32_t b = P.lvl_inner_ptr[d], e = P.lvl_inner_ptr[d + 1];
-        if (e > b)
-            hipLaunchKernelGGL((k_up<double, double>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_inner + b,
-                               dm.son0, dm.son1, E, xh, ldh);
-    }
-    return hipGetLastError();
+    return hipErrorInvalidValue;  // FP64 operators with k <= 64 only
 }
 
 hipError_t run_down_pass(const DevMat &dm, int64_t m, double *yh, int64_t ldh, hipStream_t st) {
@@ -890,14 +984,7 @@ hipError_t run_down_pass(const DevMat &dm, int64_t m, double *yh, int64_t ldh, h
         }
         return hipGetLastError();
     }
-    const unsigned gy = (unsigned)((m + TC - 1) / TC);
-    for (int d = std::max(1, P.adm_depth + 1); d <= dm.depth_max; ++d) {
-        const int32_t b = P.lvl_ptr[d], e = P.lvl_ptr[d + 1];
-        if (e > b)
-            hipLaunchKernelGGL((k_down<double, double>), dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_all + b,
-                               dm.parent, E, yh, ldh);
-    }
-    return hipGetLastError();
+    return hipErrorInvalidValue;  // FP64 operators with k <= 64 only
 }
 
 size_t matmul_ws_bytes(const DevMat &dm, int64_t m) {
@@ -918,14 +1005,11 @@ hipError_t run_matmul_cfg(const DevMat &dm, const TuneCfg &cfg, int64_t m, doubl
                           hipEvent_t *ev, const int32_t *skip) {
     switch (dm.storage) {
         case H2X_F64:
-            return matmul_typed<double, double, double>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, tree_order, ws, st,
-                                                        ev, skip);
+            return matmul_f64(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, tree_order, ws, st, ev, skip);
         case H2X_F32:
-            return matmul_typed<float, float, float>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, tree_order, ws, st, ev,
-                                                     skip);
+            return matmul_lp<float>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, tree_order, ws, st, ev, skip);
         default:
-            return matmul_typed<bf16_t, float, float>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, tree_order, ws, st, ev,
-                                                      skip);
+            return matmul_lp<bf16_t>(dm, cfg, m, alpha, X, ldx, beta, Y, ldy, tree_order, ws, st, ev, skip);
     }
 }
 

@@ -1,5 +1,5 @@
 // Transfer passes of the FP64 operator through the tensor structure of the transfer matrices
-// (Chebyshev order P = 3 or 4, rank k = P^3).  The interpolation nodes of a cluster form a
+// (Chebyshev order P = 3 to 8, rank k = P^3).  The interpolation nodes of a cluster form a
 // P x P x P Chebyshev grid on its axis-parallel box and the Lagrange polynomials are products
 // of one-dimensional ones, so the transfer matrix of a son c (the father's polynomials at the
 // son's nodes) is the Kronecker product of three P x P matrices:
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256) void k_up(int64_t m, const int32_t *__restrict
     const int32_t sc[2] = {son[2 * blockIdx.x], son[2 * blockIdx.x + 1]};
     const int64_t j0 = (int64_t)blockIdx.y * MC;
     const int mc = (int)min<int64_t>(MC, m - j0);
-    if (threadIdx.x < 2 * NF) fs[threadIdx.x] = F1[(int64_t)sc[threadIdx.x / NF] * NF + threadIdx.x % NF];
+    for (int e = threadIdx.x; e < 2 * NF; e += 256) fs[e] = F1[(int64_t)sc[e / NF] * NF + e % NF];
 #pragma unroll
     for (int u = 0; u < (NIN + 255) / 256; ++u) {
         const int idx = threadIdx.x + 256 * u;

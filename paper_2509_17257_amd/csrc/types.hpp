@@ -42,8 +42,9 @@ __host__ __device__ inline double to_double(bf16_t v) { return (double)to_float(
 
 // Coupling matrices: layout 0 is row-major k x k; layouts 2 (FP32) and 3 (BF16),
 // for k = 64, put the 16 bytes one lane of the low-precision matrix-core kernels
-// reads for one (16-row tile, k-chunk) next to each other, 64 lanes in order.  Layout 1 (k a multiple of
-// 16) is the operand order of the FP64 matrix-core coupling kernel: for each
+// reads for one (16-row tile, k-chunk) next to each other, 64 lanes in order.  Layout 1 (rows
+// padded to a multiple of 16 and columns to a multiple of 8 with zeros: s_block entries) is the
+// operand order of the FP64 matrix-core coupling kernels: for each
 // 16-row tile I and each pair of 4-column steps, the 64 lanes of a wave read
 // 2 consecutive doubles each (one 16-byte load per lane).  Within a tile
 // (I, kk2), lane l = 16 * q + r holds S[16 I + r, 8 kk2 + 4 h + q] at slot h.
@@ -60,8 +61,27 @@ __host__ __device__ inline int64_t s_index(int swz, int k, int nu, int mu) {
     }
     const int kk2 = mu >> 3, h = (mu >> 2) & 1, q = mu & 3;
     const int lane = 16 * q + r;
-    const int tiles_k2 = k >> 3;
+    const int tiles_k2 = (k + 7) >> 3;
     return (((int64_t)I * tiles_k2 + kk2) * 64 + lane) * 2 + h;
+}
+
+// entries stored per coupling matrix
+__host__ __device__ inline int64_t s_block(int swz, int k) {
+    return swz == 1 ? (int64_t)((k + 15) / 16 * 16) * ((k + 7) / 8 * 8) : (int64_t)k * k;
+}
+
+// storage index e of a coupling matrix -> (nu, mu) (inverse of s_index, layouts 0 and 1; in
+// layout 1 with padding nu or mu may be k or more)
+__host__ __device__ inline void s_coords(int swz, int k, int e, int &nu, int &mu) {
+    if (swz == 0) {
+        nu = e / k;
+        mu = e - nu * k;
+        return;
+    }
+    const int h = e & 1, lane = (e >> 1) & 63, rest = e >> 7, k8 = (k + 7) >> 3;
+    const int kk2 = rest % k8, I = rest / k8;
+    nu = 16 * I + (lane & 15);
+    mu = 8 * kk2 + 4 * h + (lane >> 4);
 }
 
 }  // namespace h2x
