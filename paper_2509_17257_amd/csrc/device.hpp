@@ -98,6 +98,7 @@ struct DevMat {
     int64_t *near_cptr = nullptr, *near_cblk = nullptr;  // near-field blocks by column leaf
     int32_t *sys_of = nullptr;   // C, system of each cluster
     int32_t *depth = nullptr;    // C, depth of each cluster
+    int32_t *leaf_of = nullptr;  // C, leaf index of each cluster (-1: inner)
     int64_t *perm = nullptr;     // n
     double *pts = nullptr;       // n x 3 tree order
     double *box = nullptr;       // C x 6

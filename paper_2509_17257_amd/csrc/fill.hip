@@ -4,6 +4,7 @@
 // operator can be tens of GB (coupling matrices dominate), so it is generated
 // where it is used, directly into the caller's workspace.
 #include <cmath>
+#include <type_traits>
 
 #include "device.hpp"
 #include "types.hpp"
@@ -188,41 +189,213 @@ __global__ void k_fill_S(int k, int kernel, double ell, double npts, const int32
         }
 }
 
+// exp(-sqrt(r2) / ell), ie = 1 / ell.  The square root by Goldschmidt's iteration from the
+// hardware's reciprocal square root, the quotient by a product and one correction; squared
+// distances and length scales near the ends of the range take the library's forms.
+__device__ inline double exp_kernel(double r2, double ell, double ie) {
+    const double y = __builtin_amdgcn_rsq(r2);
+    double g = r2 * y, h = 0.5 * y;
+    const double e0 = fma(-h, g, 0.5);
+    g = fma(g, e0, g);
+    h = fma(h, e0, h);
+    const double e1 = fma(-h, g, 0.5);
+    g = fma(g, e1, g);
+    h = fma(h, e1, h);
+    g = fma(fma(-g, g, r2), h, g);
+    if (!(r2 > 1e-280 && r2 < 1e280)) g = sqrt(r2);
+    double q;
+    if (ell > 1e-290 && ell < 1e290) {
+        q = fmin(g * ie, 1e5);  // finite (and already beyond the exponential's range)
+        q = fma(fma(-q, ell, g), ie, q);
+    } else {
+        q = g / ell;
+    }
+    return exp(-q);
+}
+
+// k_fill_S for the exponential kernel of order P, one work-group per block, in storage order (a
+// 16-byte store per thread in the matrix-core layouts; padding entries are zero).  The nodes of a
+// cluster are a tensor grid, so a squared distance is the sum of three entries of P x P tables
+// of squared one-dimensional differences (LDS).  The kernel is symmetric: where the lists are
+// (cptr given), the block (t, s) with t < s also writes the transposed block (s, t), entry i of
+// column list t for entry i of row list t, and (s, t) writes nothing.  In layout 1 a thread then
+// holds the 2 x 2 patch {nu, nu + 4} x {mu, mu + 4}, two 16-byte stores for either block.
+// Bound by the FP64 vector instructions of the square root and the exponential (about 65 an
+// entry) and by the stores: 5.57 GB of rank-64 FP64 blocks in 1.10 ms (5.0 TB/s); 1.57 ms without
+// the transposed blocks, 2.80 ms with nodes, divisions and 8-byte stores per entry.
+template <typename T, int P>
+__global__ __launch_bounds__(256) void k_fill_S_exp(double ell, const int32_t *__restrict__ adm_row,
+                                                    const int32_t *__restrict__ adm_col,
+                                                    const double *__restrict__ nodes, T *__restrict__ S, int64_t b0,
+                                                    const int64_t *__restrict__ ptr, const int64_t *__restrict__ cptr,
+                                                    const int64_t *__restrict__ cblk) {
+    constexpr int K = P * P * P, KR = (K + 15) / 16 * 16, KC = (K + 7) / 8 * 8;
+    constexpr int SWZ = K == 64 ? (sizeof(T) == 8 ? 1 : (sizeof(T) == 4 ? 2 : 3)) : (K > 64 && sizeof(T) == 8 ? 1 : 0);
+    constexpr int G = SWZ ? 16 / (int)sizeof(T) : 1;
+    constexpr int BLK = SWZ == 1 ? KR * KC : K * K;
+    constexpr bool PATCH = SWZ == 1 && KR == KC;  // orders 4, 5 and 8
+    __shared__ double d2[3][P * P];
+    const int64_t b = b0 + blockIdx.x;
+    const int32_t t = adm_row[b], s = adm_col[b];
+    const bool pair = cptr && t != s && (PATCH || SWZ == 0);
+    if (pair && t > s) return;
+    const int tid = threadIdx.x;
+    if (tid < 3 * P * P) {
+        const int d = tid / (P * P), i = tid / P % P, j = tid % P, st = d == 0 ? 1 : (d == 1 ? P : P * P);
+        const double v = nodes[((int64_t)t * K + i * st) * 3 + d] - nodes[((int64_t)s * K + j * st) * 3 + d];
+        d2[d][i * P + j] = v * v;
+    }
+    __syncthreads();
+    const double ie = 1.0 / ell;
+    T *Sb = S + b * BLK, *Sp = pair ? S + cblk[cptr[t] + (b - ptr[t])] * BLK : nullptr;
+    auto entry = [&](int nu, int mu) {
+        const bool in = K % 16 == 0 || SWZ == 0 || (nu < K && mu < K);
+        const int n1 = in ? nu : 0, m1 = in ? mu : 0;
+        const double r2 = d2[1][n1 / P % P * P + m1 / P % P] + d2[0][n1 % P * P + m1 % P] +
+                          d2[2][n1 / (P * P) * P + m1 / (P * P)];
+        return in ? exp_kernel(r2, ell, ie) : 0.0;
+    };
+    if constexpr (PATCH) {
+        typedef double dbl2 __attribute__((ext_vector_type(2)));
+        constexpr int NPAT = KR * KC / 4, NU = (NPAT + 255) / 256;
+#pragma unroll NU <= 4 ? NU : 2
+        for (int u = 0; u < NU; ++u) {
+            const int g = tid + 256 * u;
+            if (NPAT % 256 != 0 && g >= NPAT) break;
+            // patch g: rows nu, nu + 4 (8 a + 0..3 -> tile rows with bit 2 clear), columns mu, mu + 4
+            const int r4 = g & 3, q = (g >> 2) & 3, ra = (g >> 4) % (KR / 8), ca = (g >> 4) / (KR / 8);
+            const int nu = 8 * ra + r4, mu = 8 * ca + q;
+            const double v00 = entry(nu, mu), v01 = entry(nu, mu + 4), v10 = entry(nu + 4, mu), v11 = entry(nu + 4, mu + 4);
+            *(dbl2 *)(Sb + s_index(1, K, nu, mu)) = dbl2{v00, v01};
+            *(dbl2 *)(Sb + s_index(1, K, nu + 4, mu)) = dbl2{v10, v11};
+            if (pair) {
+                *(dbl2 *)(Sp + s_index(1, K, mu, nu)) = dbl2{v00, v10};
+                *(dbl2 *)(Sp + s_index(1, K, mu + 4, nu)) = dbl2{v01, v11};
+            }
+        }
+    } else {
+        constexpr int NU = (BLK / G + 255) / 256;
+#pragma unroll NU <= 8 ? NU : 4
+        for (int u = 0; u < NU; ++u) {
+            const int g = tid + 256 * u;
+            if (BLK / G % 256 != 0 && g >= BLK / G) break;
+            T v[G];
+#pragma unroll
+            for (int x = 0; x < G; ++x) {
+                int nu, mu;
+                if constexpr (SWZ == 0) {
+                    nu = g / K;
+                    mu = g % K;
+                } else if constexpr (SWZ == 1) {
+                    const int lane = g & 63, rest = g >> 6;
+                    nu = rest / (KC / 8) * 16 + (lane & 15);
+                    mu = rest % (KC / 8) * 8 + 4 * x + (lane >> 4);
+                } else {  // 4 G columns per chunk, G consecutive ones per lane
+                    constexpr int NCH = K / (4 * G);
+                    const int lane = g & 63, rest = g >> 6;
+                    nu = rest / NCH * 16 + (lane & 15);
+                    mu = rest % NCH * 4 * G + G * (lane >> 4) + x;
+                }
+                v[x] = from_double<T>(entry(nu, mu));
+            }
+            if constexpr (G == 1) {
+                Sb[g] = v[0];
+                if (pair) Sp[g % K * K + g / K] = v[0];
+            } else {
+                __builtin_memcpy(Sb + (int64_t)g * G, v, 16);
+            }
+        }
+    }
+}
+
 // N_(t,s)[i, j] = g(x_i, x_j) + shift [i == j], row-major |t| x |s|, or stored
 // transposed when trans != 0: |s| rows of length pad_rows(|t|), padding zero
 // (complex kernel: real part into N, imaginary part into N + n_plane)
+//
+// One work-group per block, in tiles of up to 64 x 64 entries in storage order, so that the
+// stores of a wave are consecutive.  Where the lists are symmetric (cptr given, real kernels),
+// the block (t, s) with t < s also writes the block (s, t) out of an LDS tile: entry i of the
+// column list of leaf t is the transposed block of entry i of its row list.
+// Bound by the evaluation (about 130 vector instructions an entry) at four work-groups per CU:
+// 1.2 GB of FP64 blocks of 43 points in 0.50 ms; 0.60 ms without the transposed blocks, 0.69 ms
+// with 64-bit divisions and 8-byte stores a block row apart.
 template <typename TN>
-__global__ void k_fill_N(int kernel, double ell, double shift, double npts, const int32_t *__restrict__ near_row,
-                         const int32_t *__restrict__ near_col, const int64_t *__restrict__ near_off,
-                         const int32_t *__restrict__ first, const int32_t *__restrict__ size,
-                         const double *__restrict__ pts, TN *__restrict__ N, int trans, int64_t n_plane) {
-    const int64_t q = blockIdx.x;
+__global__ __launch_bounds__(256) void k_fill_N(int kernel, double ell, double shift, double npts, int64_t q0,
+                                                const int32_t *__restrict__ near_row,
+                                                const int32_t *__restrict__ near_col,
+                                                const int64_t *__restrict__ near_off,
+                                                const int32_t *__restrict__ first, const int32_t *__restrict__ size,
+                                                const double *__restrict__ pts, TN *__restrict__ N, int trans,
+                                                int64_t n_plane, const int32_t *__restrict__ leaf_of,
+                                                const int64_t *__restrict__ ptr, const int64_t *__restrict__ cptr,
+                                                const int64_t *__restrict__ cblk) {
+    constexpr int TA = 64, TL = 64;
+    __shared__ TN tile[TL * (TA + 1)];
+    __shared__ double pts_a[3][TA], pts_c[3][TL];  // the tile's points
+    const int64_t q = q0 + blockIdx.x;
     const int32_t t = near_row[q], s = near_col[q];
-    const int64_t nt = size[t], ns = size[s], ft = first[t], fs = first[s];
-    TN *Nb = N + near_off[q];
-    const int64_t nt2 = pad_rows(nt);
-    const bool cplx = kernel == H2X_KERNEL_HELMHOLTZ;
-    for (int64_t e = threadIdx.x; e < nt * ns; e += blockDim.x) {
-        const int64_t il = e / ns, jl = e % ns, i = ft + il, j = fs + jl;
-        const int64_t at = trans ? jl * nt2 + il : e;
-        if (cplx) {
-            double re, im;
-            kernel_gc(ell, npts, &pts[3 * i], &pts[3 * j], re, im);
-            if (i == j) re += shift;
-            Nb[at] = (TN)re;
-            Nb[at + n_plane] = (TN)im;
-        } else {
-            double v = kernel_g(kernel, ell, &pts[3 * i], &pts[3 * j]);
-            if (i == j) v += shift;
-            Nb[at] = (TN)v;
-        }
+    const bool cplx = kernel == H2X_KERNEL_HELMHOLTZ, sym = cptr && !cplx;
+    if (sym && t > s) return;
+    TN *Nb = N + near_off[q], *Np = nullptr;
+    if (sym && t < s) {
+        const int32_t l = leaf_of[t];
+        Np = N + near_off[cblk[cptr[l] + (q - ptr[l])]];
     }
-    if (trans)
-        for (int64_t e = threadIdx.x; e < (nt2 - nt) * ns; e += blockDim.x) {
-            const int64_t at = (e / (nt2 - nt)) * nt2 + nt + e % (nt2 - nt);
-            Nb[at] = (TN)0;
-            if (cplx) Nb[at + n_plane] = (TN)0;
+    // stored rows a (ra of them) of ca entries, padded to len: transposed, the points of s by those of t
+    const int32_t ra = size[trans ? s : t], ca = size[trans ? t : s];
+    const int32_t len = trans ? (int32_t)pad_rows(ca) : ca, lenp = trans ? (int32_t)pad_rows(ra) : ra;  // (lenp: of (s, t))
+    const double *pa = pts + 3 * (int64_t)first[trans ? s : t], *pc = pts + 3 * (int64_t)first[trans ? t : s];
+    const double ie = 1.0 / ell;
+    for (int32_t a0 = 0; a0 < ra; a0 += TA)
+        for (int32_t c0 = 0; c0 < ca; c0 += TL) {
+            const int na = min(TA, ra - a0), nc = min(TL, ca - c0);
+            const int dg = t == s ? c0 - a0 : 1 << 30;  // a - c on the diagonal
+            TN *Na = Nb + (int64_t)a0 * len + c0;
+            const float inv = 1.0f / (float)nc;
+            if ((int)threadIdx.x < 3 * na) pts_a[threadIdx.x % 3][threadIdx.x / 3] = pa[3 * (int64_t)a0 + threadIdx.x];
+            if ((int)threadIdx.x < 3 * nc) pts_c[threadIdx.x % 3][threadIdx.x / 3] = pc[3 * (int64_t)c0 + threadIdx.x];
+            __syncthreads();
+            for (int e = threadIdx.x; e < na * nc; e += 256) {
+                const int a = (int)((e + 0.5f) * inv), c = e - a * nc;  // exact for e < 4096
+                const double x[3] = {pts_c[0][c], pts_c[1][c], pts_c[2][c]};
+                const double y[3] = {pts_a[0][a], pts_a[1][a], pts_a[2][a]};
+                const int64_t at = (int64_t)a * len + c;
+                const bool diag = a - c == dg;
+                if (cplx) {
+                    double re, im;
+                    kernel_gc(ell, npts, x, y, re, im);
+                    Na[at] = (TN)(diag ? re + shift : re);
+                    Na[at + n_plane] = (TN)im;
+                    continue;
+                }
+                double v;
+                if (kernel == H2X_KERNEL_EXP) {
+                    const double dx = x[0] - y[0], dy = x[1] - y[1], dz = x[2] - y[2];
+                    v = exp_kernel(dx * dx + dy * dy + dz * dz, ell, ie);
+                } else {
+                    v = kernel_g(kernel, ell, x, y);
+                }
+                if (diag) v += shift;
+                Na[at] = (TN)v;
+                if (Np) tile[c * (TA + 1) + a] = (TN)v;
+            }
+            __syncthreads();
+            if (!Np) continue;
+            const float invp = 1.0f / (float)na;
+            for (int e = threadIdx.x; e < na * nc; e += 256) {
+                const int c = (int)((e + 0.5f) * invp), a = e - c * na;
+                Np[(int64_t)(c0 + c) * lenp + a0 + a] = tile[c * (TA + 1) + a];
+            }
+            __syncthreads();
         }
+    // padding
+    if (len > ca)
+        for (int32_t a = threadIdx.x; a < ra; a += 256) {
+            Nb[(int64_t)a * len + ca] = (TN)0;
+            if (cplx) Nb[(int64_t)a * len + ca + n_plane] = (TN)0;
+        }
+    if (Np && lenp > ra)
+        for (int32_t c = threadIdx.x; c < ca; c += 256) Np[(int64_t)c * lenp + ra] = (TN)0;
 }
 
 // coupling matrices and near field, system by system (each with its own kernel
@@ -237,14 +410,32 @@ hipError_t fill_SN(const DevMat &dm, hipStream_t st) {
         const int64_t a = P.sys_adm[i], na = P.sys_adm[i + 1] - a;
         const int64_t q = P.sys_near[i], nq = P.sys_near[i + 1] - q;
         const double npts = (double)(P.sys_row[i + 1] - P.sys_row[i]);  // points of system i
-        if (na > 0)
+        // the exponential kernel in its own form per order
+        auto fill_exp = [&](auto Pc) {
+            hipLaunchKernelGGL((k_fill_S_exp<T, decltype(Pc)::value>), dim3((unsigned)na), dim3(256), 0, st, ell,
+                               dm.adm_row, dm.adm_col, dm.nodes, (T *)dm.S, a, dm.adm_ptr,
+                               P.sym_lists ? dm.adm_cptr : nullptr, dm.adm_cblk);
+        };
+        if (na > 0 && kernel == H2X_KERNEL_EXP)
+            switch (dm.p) {
+                case 1: fill_exp(std::integral_constant<int, 1>{}); break;
+                case 2: fill_exp(std::integral_constant<int, 2>{}); break;
+                case 3: fill_exp(std::integral_constant<int, 3>{}); break;
+                case 4: fill_exp(std::integral_constant<int, 4>{}); break;
+                case 5: fill_exp(std::integral_constant<int, 5>{}); break;
+                case 6: fill_exp(std::integral_constant<int, 6>{}); break;
+                case 7: fill_exp(std::integral_constant<int, 7>{}); break;
+                default: fill_exp(std::integral_constant<int, 8>{}); break;
+            }
+        else if (na > 0)
             hipLaunchKernelGGL(k_fill_S<T>, dim3((unsigned)na), dim3(256), 0, st, dm.k, kernel, ell, npts,
                                dm.adm_row + a, dm.adm_col + a, dm.nodes, (T *)dm.S + a * dm.s_blk, dm.swz, dm.s_blk,
                                dm.s_plane);
         if (nq > 0)
-            hipLaunchKernelGGL(k_fill_N<TN>, dim3((unsigned)nq), dim3(256), 0, st, kernel, ell, shift, npts,
-                               dm.near_row + q, dm.near_col + q, dm.near_off + q, dm.first, dm.size, dm.pts,
-                               (TN *)dm.N, dm.near_t, dm.n_plane);
+            hipLaunchKernelGGL(k_fill_N<TN>, dim3((unsigned)nq), dim3(256), 0, st, kernel, ell, shift, npts, q,
+                               dm.near_row, dm.near_col, dm.near_off, dm.first, dm.size, dm.pts, (TN *)dm.N,
+                               dm.near_t, dm.n_plane, dm.leaf_of, dm.near_ptr, P.sym_lists ? dm.near_cptr : nullptr,
+                               dm.near_cblk);
     }
     return hipGetLastError();
 }
@@ -331,6 +522,7 @@ size_t mat_layout(const Plan &P, h2x_prec storage, DevMat *dm, char *base) {
     d.near_cblk = carve<int64_t>(cur, base, nn + 1);
     d.sys_of = carve<int32_t>(cur, base, C);
     d.depth = carve<int32_t>(cur, base, C);
+    d.leaf_of = carve<int32_t>(cur, base, C);
     d.perm = carve<int64_t>(cur, base, n);
     d.pts = carve<double>(cur, base, 3 * n);
     d.box = carve<double>(cur, base, 6 * (size_t)C);

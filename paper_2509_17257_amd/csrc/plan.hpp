@@ -68,6 +68,10 @@ struct Plan {
     std::vector<int64_t> near_cptr; // L + 1
     std::vector<int64_t> near_cblk; // n_near
 
+    // entry i of the column list of every cluster (leaf) is the transposed block of entry i of
+    // its row list: always, as the admissibility condition is symmetric in the two clusters
+    bool sym_lists = false;
+
     // launch order of the row clusters in the coupling stage: the rows are cut
     // into 8 contiguous eighths (one per XCD), longest list first within each
     std::vector<int32_t> cpl_order; // C

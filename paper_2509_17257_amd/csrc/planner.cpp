@@ -127,6 +127,26 @@ void leaf_order(Plan &P) {
     }
 }
 
+// whether the i-th block of every column list is the transposed block of the i-th block of the
+// same cluster's row list (both lists in cluster order)
+bool symmetric_lists(const Plan &P) {
+    for (int32_t t = 0; t < P.C; ++t) {
+        if (P.adm_ptr[t + 1] - P.adm_ptr[t] != P.adm_cptr[t + 1] - P.adm_cptr[t]) return false;
+        for (int64_t b = P.adm_ptr[t], q = P.adm_cptr[t]; b < P.adm_ptr[t + 1]; ++b, ++q) {
+            const int32_t s = P.adm_col[b];
+            if (P.adm_cblk[q] < P.adm_ptr[s] || P.adm_cblk[q] >= P.adm_ptr[s + 1]) return false;
+        }
+    }
+    for (size_t l = 0; l < P.leaves.size(); ++l) {
+        if (P.near_ptr[l + 1] - P.near_ptr[l] != P.near_cptr[l + 1] - P.near_cptr[l]) return false;
+        for (int64_t b = P.near_ptr[l], q = P.near_cptr[l]; b < P.near_ptr[l + 1]; ++b, ++q) {
+            const int32_t ls = P.leaf_index[P.near_col[b]];
+            if (P.near_cblk[q] < P.near_ptr[ls] || P.near_cblk[q] >= P.near_ptr[ls + 1]) return false;
+        }
+    }
+    return true;
+}
+
 }  // namespace
 
 Plan *build_plan(const double *pts, int64_t n, const h2x_params &prm, std::string &err) {
@@ -334,6 +354,7 @@ Plan *build_plan(const double *pts, int64_t n, const h2x_params &prm, std::strin
 
     coupling_order(*P);
     leaf_order(*P);
+    P->sym_lists = symmetric_lists(*P);
     P->sys_prm.assign(1, prm);
     P->sys_row = {0, n};
     P->sys_C = {0, (int64_t)C};
@@ -452,6 +473,7 @@ Plan *merge_plans(const std::vector<const Plan *> &parts, std::string &err) {
     }
     coupling_order(*P);
     leaf_order(*P);
+    P->sym_lists = symmetric_lists(*P);
     return P;
 }
 
