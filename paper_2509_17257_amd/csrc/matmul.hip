@@ -716,7 +716,7 @@ void matmul_gen_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alph
     mark(1);
     gen_up_levels(dm, m, xh, ldh, st, sk);
     mark(2);
-    launch_coupling_rows(dm, m, xh, yh, ldh, st, sk);
+    launch_coupling_rows(dm, m, xh, yh, ldh, st, sk, cfg.nj_coupling);
     mark(3);
     gen_down_levels(dm, m, yh, ldh, st, sk);
     mark(4);
