@@ -194,243 +194,268 @@ __global__ __launch_bounds__(256) void k_tsmm(int64_t n, int m, const double *__
     }
 }
 
-// ---- m x m steps: right-looking, four waves, one barrier per step ----
+// ---- m x m steps: one work-group of eight waves, rows in registers ----
 //
-// Wave w takes the rows congruent to w modulo 4 and lane j the column j of the step's
-// update, so a step is one pass of independent multiply-adds over the trailing part; a value
-// that the step reads (the pivot column, the pivot row) is scaled where it is read and
-// written back scaled in the next step, which no longer reads it.  kMaxM >= m, so a column
-// index is a lane index.
+// All three factorizations are the elimination of an augmented matrix [S | I]: step k takes a
+// pivot row b, and every row i not yet taken subtracts S[i][b] / S[b][b] times it from both
+// halves.  The right half becomes A with A S A^T = D (the inverse of the unit triangular
+// factor), so with Abar = D^{-1/2} A
+//   S^{-1} = Abar^T Abar     (the solve: two products)   and
+//   M = Abar^T, M^T S M = I  (Cholesky QR: P = Z M),
+// in the original row numbering, without a substitution sweep and without square roots in the
+// chain.  Row i lives in register i / 8 of wave i % 8, one column per lane (kMaxM >= m lanes); the
+// pivot row goes to the other waves through LDS (double-buffered: one barrier a step), its
+// entries are the columns' multipliers by symmetry (read across lanes into scalars), and every
+// wave follows the remaining diagonal in a register of its own, so that the pivot search needs
+// no exchange.
+//
+// Bound by the latency of a step (LDS write, barrier, LDS read, one reciprocal, the rows of a
+// wave).  m = 32: first pass 28 us, second 17, solve 17, solve with the stored factor 8; 60, 33, 40
+// and 26 as right-looking Cholesky in LDS with triangular solves (three to two sweeps of m steps);
+// 4 or 16 waves: second pass 23 and 17, first 35 and 31.
+constexpr int kW = 8, kR = kMaxM / kW;  // waves, rows per wave
 
-// C = sign * G^{-1} F on the active index set (Cholesky of G restricted to it);
-// inactive rows of C are zero.  Sets breakdown if G is not positive definite there.  The
-// factor is stored in Lc (lower triangle, row stride m, diagonal included); with reuse the
-// factor stored by the previous call (same G, same active set) is taken instead.
-__global__ __launch_bounds__(256) void k_bcg_solve(int m, const double *__restrict__ G, const double *__restrict__ F,
-                                                   double *__restrict__ Cm, double sign, BcgState *st,
-                                                   double *__restrict__ Lc, int reuse, const int32_t *stop) {
+__device__ inline double lane_value(double v, int l) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, l);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), l);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// largest value over the wave of a 32-bit key, by lane shifts inside the rows of 16 and two row
+// broadcasts (a lane without a source keeps its own value); lane 63 ends with it
+__device__ inline uint32_t wave_max(uint32_t v) {
+    auto step = [&](uint32_t moved) { v = max(v, moved); };
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xf, 0xf, false));  // row_shr:1
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x112, 0xf, 0xf, false));  // row_shr:2
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x114, 0xf, 0xf, false));  // row_shr:4
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x118, 0xf, 0xf, false));  // row_shr:8
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// 1 / v by two Newton steps from the hardware's reciprocal; v = 0 gives infinity
+__device__ inline double recip(double v) {
+    double y = __builtin_amdgcn_rcp(v);
+    const double y1 = fma(fma(-v, y, 1.0), y, y), y2 = fma(fma(-v, y1, 1.0), y1, y1);
+    return v > 1e-290 && v < 1e290 ? y2 : 1.0 / v;
+}
+
+struct Elim {
+    double s[kR], a[kR];  // rows w + 8 r of S and A, column `lane`
+    double rv;            // lane b: 1 / S[b][b] of a taken row b
+    uint64_t taken, skip;  // rows taken; rows that no step changes any more (taken or left out)
+};
+
+// one step: row b is the pivot; zero: the value that stands in for a pivot that is not positive
+// (rinv = 1 / zero); returns whether the pivot is positive
+__device__ inline bool elim_step(Elim &e, int k, int b, double zero, double (*rows)[2][kMaxM]) {
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double(&row)[2][kMaxM] = rows[k & 1];
+    if (w == (b & (kW - 1))) {
+        double s = e.s[0], a = e.a[0];
+#pragma unroll
+        for (int r = 1; r < kR; ++r) {
+            s = (b / kW) == r ? e.s[r] : s;
+            a = (b / kW) == r ? e.a[r] : a;
+        }
+        row[0][lane] = s;
+        row[1][lane] = a;
+    }
+    __syncthreads();
+    const double p = row[0][lane], q = row[1][lane], v = lane_value(p, b);
+    const bool pos = v > 0.0;
+    const double ri = recip(pos ? v : zero);
+    e.rv = lane == b ? ri : e.rv;
+    e.taken |= 1ull << b;
+    e.skip |= 1ull << b;
+    const double g = p * ri;  // lane i: the multiplier of row i
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+        const int i = w + kW * r;
+        if (!((e.skip >> i) & 1)) {  // (wave-uniform)
+            const double f = -lane_value(g, i);
+            e.s[r] = fma(f, p, e.s[r]);
+            e.a[r] = fma(f, q, e.a[r]);
+        }
+    }
+    return pos;
+}
+
+// keep: the rows that take part
+__device__ inline void elim_load(Elim &e, int m, const double *__restrict__ S, uint64_t keep) {
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+        const int i = w + kW * r;
+        e.s[r] = i < m && lane < m ? S[i * m + lane] : 0.0;
+        e.a[r] = i == lane ? 1.0 : 0.0;
+    }
+    e.rv = 0.0;
+    e.taken = 0;
+    e.skip = ~keep;
+}
+
+// row i of Abar, column `lane` (zero where row i was not taken)
+__device__ inline double elim_row(const Elim &e, int r, double sq) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = w + kW * r;
+    return (e.taken >> i) & 1 ? e.a[r] * lane_value(sq, i) : 0.0;
+}
+
+// C = sign * Abar^T (Abar F): Abar in LDS (zero-padded), F and C m x m in memory
+__device__ inline void solve_apply(int m, double (*Ab)[kMaxM + 1], double (*U)[kMaxM + 1], const double *__restrict__ F,
+                                   double *__restrict__ Cm, double sign) {
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int mt = (m + 15) / 16, kp = 16 * mt;
+    for (int i = w; i < kp; i += kW) U[i][lane] = i < m && lane < m ? F[i * m + lane] : 0.0;
+    __syncthreads();
+    dbl4 acc[16 / kW];
+    auto product = [&](bool trans) {
+#pragma unroll
+        for (int h = 0; h < 16 / kW; ++h) {
+            const int tl = w + kW * h;
+            if (tl >= mt * mt) break;
+            const int I = tl / mt, J = tl % mt;
+            dbl4 c = dbl4{0.0, 0.0, 0.0, 0.0};
+            for (int k = 0; k < kp; k += 4)
+                c = __builtin_amdgcn_mfma_f64_16x16x4f64(trans ? Ab[k + lq][16 * I + lr] : Ab[16 * I + lr][k + lq],
+                                                         U[k + lq][16 * J + lr], c, 0, 0, 0);
+            acc[h] = c;
+        }
+    };
+    product(false);
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 16 / kW; ++h) {
+        const int tl = w + kW * h;
+        if (tl >= mt * mt) break;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) U[16 * (tl / mt) + lq + 4 * r][16 * (tl % mt) + lr] = acc[h][r];
+    }
+    __syncthreads();
+    product(true);
+#pragma unroll
+    for (int h = 0; h < 16 / kW; ++h) {
+        const int tl = w + kW * h;
+        if (tl >= mt * mt) break;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * (tl / mt) + lq + 4 * r, j = 16 * (tl % mt) + lr;
+            if (i < m && j < m) Cm[i * m + j] = sign * acc[h][r];
+        }
+    }
+}
+
+// C = sign * G^{-1} F on the active index set; inactive rows of C are zero.  Sets breakdown if G
+// is not positive definite there.  Abar is stored in Lc (m x m); with reuse the one stored by
+// the previous call (same G, same active set) is taken instead.
+__global__ __launch_bounds__(64 * kW) void k_bcg_solve(int m, const double *__restrict__ G, const double *__restrict__ F,
+                                                       double *__restrict__ Cm, double sign, BcgState *st,
+                                                       double *__restrict__ Lc, int reuse, const int32_t *stop) {
     if (stop && *stop) return;
-    __shared__ double L[kMaxM][kMaxM + 1], Y[kMaxM][kMaxM + 1];
-    __shared__ double inv[kMaxM], dgv[kMaxM];
-    __shared__ int idx[kMaxM], pos[kMaxM];
-    __shared__ int r, bad;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    if (w == 0) {
-        const bool a = lane < m && st->active[lane] != 0;
-        const unsigned long long am = __ballot(a);
-        const int p = __popcll(am & ((1ull << lane) - 1ull));
-        if (a) idx[p] = lane;
-        pos[lane] = a ? p : -1;
-        if (lane == 0) {
-            r = __popcll(am);
-            bad = 0;
-        }
-    }
-    __syncthreads();
-    const int rr = r;
-    // G on the active set (or the stored factor) and the rows of F on it
-    for (int i = w; i < rr; i += 4) {
-        if (lane < rr) L[i][lane] = reuse ? (lane <= i ? Lc[i * m + lane] : 0.0) : G[idx[i] * m + idx[lane]];
-        if (lane < m) Y[i][lane] = F[idx[i] * m + lane];
-    }
-    __syncthreads();
-    if (!reuse) {
-        // right-looking Cholesky: step k updates the trailing lower triangle with the scaled
-        // column k and finalises column k - 1
-        for (int k = 0; k < rr; ++k) {
-            const double v = L[k][k];
-            const double dk = sqrt(v > 0.0 ? v : 1.0), ik = 1.0 / dk;
-            if (k > 0 && w == 0) {  // column k - 1, which this step no longer reads
-                if (lane == k - 1) L[k - 1][k - 1] = dgv[k - 1];
-                else if (lane >= k && lane < rr) L[lane][k - 1] *= inv[k - 1];
-            }
-            const double sj = lane > k && lane < rr ? L[lane][k] * ik : 0.0;
-            for (int i = k + 1 + w; i < rr; i += 4) {
-                const double si = L[i][k] * ik;
-                if (lane > k && lane <= i) L[i][lane] -= si * sj;
-            }
-            if (tid == 0) {
-                inv[k] = ik;
-                dgv[k] = dk;
-                if (!(v > 0.0)) bad = 1;
-            }
-            __syncthreads();
-        }
-        if (rr > 0 && tid == 0) L[rr - 1][rr - 1] = dgv[rr - 1];
-        if (tid == 0 && bad) st->breakdown = 1;
-        __syncthreads();
-        for (int i = w; i < rr; i += 4)
-            if (lane <= i) Lc[i * m + lane] = L[i][lane];
+    __shared__ double Ab[kMaxM][kMaxM + 1], U[kMaxM][kMaxM + 1];
+    __shared__ double rows[2][2][kMaxM];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (reuse) {
+        for (int i = w; i < kMaxM; i += kW) Ab[i][lane] = i < m && lane < m ? Lc[i * m + lane] : 0.0;
     } else {
-        for (int k = tid; k < rr; k += 256) inv[k] = 1.0 / L[k][k];
-        __syncthreads();
-    }
-    // forward substitution L Z = Y, then back substitution L^T X = Z, one column per lane;
-    // row q is scaled by 1 / L[q][q] where it is read and written back scaled one step later
-    for (int q = 0; q < rr; ++q) {
-        if (lane < m) {
-            if (q > 0 && w == 0) Y[q - 1][lane] *= inv[q - 1];
-            const double yq = Y[q][lane] * inv[q];
-            for (int a = q + 1 + w; a < rr; a += 4) Y[a][lane] -= L[a][q] * yq;
+        uint64_t left = __ballot(lane < m && st->active[lane] != 0);
+        Elim e;
+        elim_load(e, m, G, left);
+        bool ok = true;
+        for (int k = 0; left; ++k) {
+            const int b = __ffsll((unsigned long long)left) - 1;
+            left &= left - 1;
+            ok = elim_step(e, k, b, 1.0, rows) && ok;
         }
-        __syncthreads();
-    }
-    if (rr > 0 && w == 0 && lane < m) Y[rr - 1][lane] *= inv[rr - 1];
-    __syncthreads();
-    for (int a = rr - 1; a >= 0; --a) {
-        if (lane < m) {
-            if (a < rr - 1 && w == 0) Y[a + 1][lane] *= inv[a + 1];
-            const double xa = Y[a][lane] * inv[a];
-            for (int q = w; q < a; q += 4) Y[q][lane] -= L[a][q] * xa;
+        if (!ok && threadIdx.x == 0) st->breakdown = 1;
+        const double sq = sqrt(e.rv);
+#pragma unroll
+        for (int r = 0; r < kR; ++r) {
+            const int i = w + kW * r;
+            const double v = elim_row(e, r, sq);
+            Ab[i][lane] = v;
+            if (i < m && lane < m) Lc[i * m + lane] = v;
         }
-        __syncthreads();
     }
-    if (rr > 0 && w == 0 && lane < m) Y[0][lane] *= inv[0];
-    __syncthreads();
-    if (lane < m)
-        for (int j = w; j < m; j += 4) Cm[(int64_t)j * m + lane] = pos[j] >= 0 ? sign * Y[pos[j]][lane] : 0.0;
+    solve_apply(m, Ab, U, F, Cm, sign);
 }
 
-// M = T^{-1} scattered to M[piv[a]][piv[q]] (all other entries zero) for the upper-triangular
-// T of a Cholesky-QR pass in pivot order (T[a][c] = tf(a, c) for a < c, diagonal dg): back
-// substitution on the identity, one column per lane, row a scaled where it is read.
-template <typename TF>
-__device__ inline void tinv_scatter(int m, int r, TF tf, const double *dg, const int *piv, double *M,
-                                    double (*Z)[kMaxM + 1], double *invd) {
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    for (int e = tid; e < m * m; e += 256) M[e] = 0.0;
-    for (int a = w; a < r; a += 4)
-        if (lane < r) Z[a][lane] = a == lane ? 1.0 : 0.0;
-    for (int a = tid; a < r; a += 256) invd[a] = 1.0 / dg[a];
-    __syncthreads();
-    for (int a = r - 1; a >= 0; --a) {
-        if (lane < r) {
-            if (a < r - 1 && w == 0) Z[a + 1][lane] *= invd[a + 1];
-            const double xa = Z[a][lane] * invd[a];
-            for (int c = w; c < a; c += 4) Z[c][lane] -= tf(c, a) * xa;
-        }
-        __syncthreads();
+// M = Abar^T
+__device__ inline void elim_store(const Elim &e, int m, double *__restrict__ M) {
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const double sq = sqrt(e.rv);
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+        const int i = w + kW * r;
+        const double v = elim_row(e, r, sq);
+        if (i < m && lane < m) M[lane * m + i] = v;
     }
-    if (r > 0 && w == 0 && lane < r) Z[0][lane] *= invd[0];
-    __syncthreads();
-    if (lane < r)
-        for (int a = w; a <= lane; a += 4) M[(int64_t)piv[a] * m + piv[lane]] = Z[a][lane];
 }
 
-// first Cholesky-QR pass: pivoted Cholesky of W = Z^T Z with deflation, right-looking on the
-// Schur complement S (kept in place of W): the pivot of step k is the first column, in column
-// order, of largest remaining diagonal among those not yet taken (a NaN in the first
-// candidate stays chosen); a remaining diagonal at or below kDrop^2 of the largest diagonal
-// entry of W ends the factorization.  Row k of the factor: lv[k][j] = S[j][b] / sqrt(S[b][b]).
-__global__ __launch_bounds__(256) void k_bcg_orth1(int m, const double *__restrict__ W, double *__restrict__ M,
-                                                   BcgState *st, const int32_t *gate) {
+// first Cholesky-QR pass: pivoted factorization of W = Z^T Z with deflation: the pivot of a step
+// is the first column, in column order, of largest remaining diagonal among those not yet
+// taken (a NaN in the first candidate ends the factorization, other NaN are passed over); a
+// remaining diagonal at or below kDrop^2 of the largest diagonal entry of W ends it.
+__global__ __launch_bounds__(64 * kW) void k_bcg_orth1(int m, const double *__restrict__ W, double *__restrict__ M,
+                                                       BcgState *st, const int32_t *gate) {
     if (gate && *gate) return;
-    __shared__ double S[kMaxM][kMaxM + 1], lv[kMaxM][kMaxM + 1];
-    __shared__ double dg[kMaxM], invd[kMaxM];
-    __shared__ int piv[kMaxM], act[kMaxM];
-    __shared__ int rank, best;
-    __shared__ double dmax;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    for (int i = w; i < m; i += 4)
-        if (lane < m) S[i][lane] = W[i * m + lane];
-    if (tid < kMaxM) act[tid] = 0;
-    __syncthreads();
-    if (w == 0) {
-        // largest diagonal entry (fmax ignores NaN: any order gives the value of a scan from 0)
-        double d = lane < m ? S[lane][lane] : 0.0;
+    __shared__ double rows[2][2][kMaxM];
+    const int lane = threadIdx.x & 63;
+    Elim e;
+    elim_load(e, m, W, __ballot(lane < m));
+    double dg = lane < m ? W[lane * m + lane] : 0.0;  // the remaining diagonal
+    double dmax = 0.0;
+    {
+        double d = dg;  // (fmax ignores NaN)
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) d = fmax(d, __shfl_xor(d, o));
-        if (lane == 0) {
-            dmax = fmax(0.0, d);
-            rank = 0;
-        }
+        dmax = fmax(0.0, d);
     }
-    __syncthreads();
+    int piv = -1, rank = 0;  // lane k: the pivot of step k
     for (int k = 0; k < m; ++k) {
-        if (w == 0) {
-            const bool cand = lane < m && !act[lane];
-            const double d = cand ? S[lane][lane] : 0.0;
-            const unsigned long long cm = __ballot(cand);
-            int b = -1;
-            if (cm != 0) {
-                const int j0 = __ffsll(cm) - 1;
-                if (isnan(S[j0][j0])) {
-                    b = j0;
-                } else {
-                    // the largest value among the candidates that are numbers, then the first
-                    // lane that holds it (at least one candidate is a number here)
-                    const bool ok = cand && !isnan(d);
-                    double v = ok ? d : -INFINITY;
-#pragma unroll
-                    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-                    b = __ffsll(__ballot(ok && d == v)) - 1;
-                }
-            }
-            if (lane == 0) {
-                if (b < 0 || !(dmax > 0.0) || !(S[b][b] > kDrop * kDrop * dmax)) {
-                    best = -1;
-                } else {
-                    best = b;
-                    act[b] = 1;
-                    piv[k] = b;
-                    dg[k] = sqrt(S[b][b]);
-                    rank = k + 1;
-                }
-            }
-        }
-        __syncthreads();
-        const int b = best;
-        if (b < 0) break;
-        // row k of the factor, then the Schur complement of the columns not yet taken
-        const double ik = 1.0 / dg[k];
-        const bool free_j = lane < m && !act[lane];
-        const double sj = free_j ? S[lane][b] * ik : 0.0;
-        if (w == 0 && lane < m) lv[k][lane] = lane == b ? dg[k] : sj;
-        for (int i = w; i < m; i += 4)
-            if (free_j && !act[i]) S[i][lane] -= (S[i][b] * ik) * sj;
-        __syncthreads();
+        const bool cand = lane < m && !((e.taken >> lane) & 1);
+        const unsigned long long cm = __ballot(cand);
+        const int j0 = __ffsll(cm) - 1;
+        const unsigned long long nan = __ballot(cand && dg != dg);
+        if (!(dmax > 0.0) || ((nan >> j0) & 1)) break;
+        // the largest candidate above the threshold (positive: ordered as its bits), its high and
+        // then its low word, and the first lane that holds it
+        const bool ok = cand && dg > kDrop * kDrop * dmax;
+        if (__ballot(ok) == 0) break;
+        const uint64_t key = ok ? __builtin_bit_cast(uint64_t, dg) : 0;
+        const uint32_t hi = wave_max((uint32_t)(key >> 32));
+        const bool top = ok && (uint32_t)(key >> 32) == hi;
+        const uint32_t lo = wave_max(top ? (uint32_t)key : 0u);
+        const int b = __ffsll(__ballot(top && (uint32_t)key == lo)) - 1;
+        elim_step(e, k, b, 0.0, rows);
+        // (row b of S, still in LDS: the buffer of step k is written again two barriers later)
+        const double p = rows[k & 1][0][lane];
+        dg -= p * (p * lane_value(e.rv, b));
+        piv = lane == k ? b : piv;
+        rank = k + 1;
     }
-    const int r = rank;
-    tinv_scatter(
-        m, r, [&](int a, int c) { return lv[a][piv[c]]; }, dg, piv, M, S, invd);
-    if (tid == 0) st->rank = r;
-    if (tid < m) {
-        st->active[tid] = act[tid];
-        st->piv[tid] = tid < r ? piv[tid] : -1;
+    elim_store(e, m, M);
+    if (threadIdx.x == 0) st->rank = rank;
+    if (threadIdx.x < m) {
+        st->active[lane] = (int32_t)((e.taken >> lane) & 1);
+        st->piv[lane] = piv;
     }
 }
 
-// second Cholesky-QR pass: plain Cholesky of W2 = P1^T P1 on the kept columns in pivot order
-// (right-looking, as in k_bcg_solve); T = L^T.
-__global__ __launch_bounds__(256) void k_bcg_orth2(int m, const double *__restrict__ W, double *__restrict__ M,
-                                                   const BcgState *st, const int32_t *stop) {
+// second Cholesky-QR pass: W2 = P1^T P1 on the kept columns, in pivot order
+__global__ __launch_bounds__(64 * kW) void k_bcg_orth2(int m, const double *__restrict__ W, double *__restrict__ M,
+                                                       const BcgState *st, const int32_t *stop) {
     if (stop && *stop) return;
-    __shared__ double L[kMaxM][kMaxM + 1], Z[kMaxM][kMaxM + 1];
-    __shared__ double dg[kMaxM], inv[kMaxM];
-    __shared__ int piv[kMaxM];
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = st->rank;
-    if (tid < r) piv[tid] = st->piv[tid];
-    __syncthreads();
-    for (int i = w; i < r; i += 4)
-        if (lane < r) L[i][lane] = W[piv[i] * m + piv[lane]];
-    __syncthreads();
-    for (int k = 0; k < r; ++k) {
-        const double v = L[k][k];
-        const double dk = sqrt(v > 0.0 ? v : 0.0), ik = 1.0 / dk;
-        if (k > 0 && w == 0 && lane >= k && lane < r) L[lane][k - 1] *= inv[k - 1];
-        const double sj = lane > k && lane < r ? L[lane][k] * ik : 0.0;
-        for (int i = k + 1 + w; i < r; i += 4) {
-            const double si = L[i][k] * ik;
-            if (lane > k && lane <= i) L[i][lane] -= si * sj;
-        }
-        if (tid == 0) {
-            inv[k] = ik;
-            dg[k] = dk;
-        }
-        __syncthreads();
-    }
-    tinv_scatter(
-        m, r, [&](int a, int c) { return L[c][a]; }, dg, piv, M, Z, inv);
+    __shared__ double rows[2][2][kMaxM];
+    const int lane = threadIdx.x & 63, r = st->rank;
+    const int piv = lane < r ? st->piv[lane] : 0;
+    Elim e;
+    elim_load(e, m, W, __ballot(lane < m && st->active[lane] != 0));
+    for (int k = 0; k < r; ++k) elim_step(e, k, __builtin_amdgcn_readlane(piv, k), 0.0, rows);
+    elim_store(e, m, M);
 }
 
 // convergence from the diagonal of R^T R
@@ -559,15 +584,15 @@ h2x_status run_block_cg_shared(const DevMat &dm, const h2x_cg_params &prm, int64
     };
     // the second solve of an iteration has the same G and active set: it takes the factor
     auto solve = [&](double sign, int reuse) {
-        hipLaunchKernelGGL(k_bcg_solve, dim3(1), dim3(256), 0, st, mi, (const double *)w.G, (const double *)w.F, w.C,
+        hipLaunchKernelGGL(k_bcg_solve, dim3(1), dim3(64 * kW), 0, st, mi, (const double *)w.G, (const double *)w.F, w.C,
                            sign, w.st, w.Lc, reuse, sp);
     };
     auto orth = [&](const double *Zs) {
         gram2(Zs, Zs, nullptr, nullptr, w.Wm, nullptr);
-        hipLaunchKernelGGL(k_bcg_orth1, dim3(1), dim3(256), 0, st, mi, (const double *)w.Wm, w.M, w.st, sp);
+        hipLaunchKernelGGL(k_bcg_orth1, dim3(1), dim3(64 * kW), 0, st, mi, (const double *)w.Wm, w.M, w.st, sp);
         tsmm(Zs, w.M, nullptr, w.P1, 1.0, 0.0);
         gram2(w.P1, w.P1, nullptr, nullptr, w.Wm, nullptr);
-        hipLaunchKernelGGL(k_bcg_orth2, dim3(1), dim3(256), 0, st, mi, (const double *)w.Wm, w.M,
+        hipLaunchKernelGGL(k_bcg_orth2, dim3(1), dim3(64 * kW), 0, st, mi, (const double *)w.Wm, w.M,
                            (const BcgState *)w.st, sp);
         tsmm(w.P1, w.M, nullptr, w.P, 1.0, 0.0);
     };
