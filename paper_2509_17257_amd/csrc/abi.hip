@@ -224,6 +224,33 @@ h2x_status h2x_mat_create(const h2x_plan *plan, h2x_prec storage, void *dev_ws, 
     for (int32_t i = 0; i < P.C; ++i) dn_par[i] = P.parent[P.lvl_all[i]];
     up(d.up_son, up_son);
     up(d.dn_par, dn_par);
+    // subtree ranges in the level lists: a level lists the clusters in pre-order, so the clusters
+    // below an entry follow those below the entry before it
+    auto ranges = [&](const std::vector<int32_t> &list, const std::vector<int32_t> &ptr, bool inner) {
+        std::vector<int32_t> rng(4 * list.size() + 1, 0), kids(list.size(), 0), first(list.size() + 1, 0);
+        for (int32_t lv = 0; lv + 1 < (int32_t)ptr.size(); ++lv) {
+            int32_t at = ptr[lv + 1];
+            for (int32_t i = ptr[lv]; i < ptr[lv + 1]; ++i) {
+                first[i] = at;
+                for (int32_t s : {P.son0[list[i]], P.son1[list[i]]})
+                    if (s >= 0 && (!inner || P.son0[s] >= 0)) ++kids[i];
+                at += kids[i];
+            }
+        }
+        for (size_t i = 0; i < list.size(); ++i) {
+            const int32_t a = first[i], b = a + kids[i];
+            rng[4 * i] = a;
+            rng[4 * i + 1] = b;
+            rng[4 * i + 2] = b > a ? first[a] : 0;
+            rng[4 * i + 3] = b > a ? first[b - 1] + kids[b - 1] : 0;
+        }
+        return rng;
+    };
+    const std::vector<int32_t> up_rng = ranges(P.lvl_inner, P.lvl_inner_ptr, true);
+    std::vector<int32_t> dn_rng = ranges(P.lvl_all, P.lvl_ptr, false);
+    dn_rng.pop_back();
+    up(d.up_rng, up_rng);
+    up(d.dn_rng, dn_rng);
     up(d.adm_ptr, P.adm_ptr);
     up(d.adm_col, P.adm_col);
     up(d.adm_row, adm_row);

@@ -81,6 +81,9 @@ struct DevMat {
     int32_t *leaves = nullptr, *lvl_all = nullptr, *lvl_inner = nullptr;
     int32_t *up_son = nullptr;  // 2 per entry of lvl_inner: its two sons
     int32_t *dn_par = nullptr;  // per entry of lvl_all: its parent (-1 at the root)
+    // 4 per entry of lvl_inner / lvl_all: the ranges [0, 1), [2, 3) of entries of its subtree one
+    // level and two levels deeper
+    int32_t *up_rng = nullptr, *dn_rng = nullptr;
     int64_t *adm_ptr = nullptr;  // C + 1
     int32_t *adm_col = nullptr;  // n_adm
     int32_t *adm_row = nullptr;  // n_adm (row cluster of each block)

@@ -44,13 +44,6 @@ __global__ void k_pack_bf16(int64_t cnt4, const float4 *__restrict__ x, uint2 *_
                        (uint32_t)bf16_bits(v.z) | ((uint32_t)bf16_bits(v.w) << 16)};
     }
 }
-// transfer levels of the FP64 operators with p = 3 and 4 through the Kronecker factors of E
-// (kron::) instead of the dense transfer matrices on the matrix cores (mfma::k_up64 / k_down64,
-// mfma::k_up / k_down)
-constexpr bool kKronTransfer = true;
-// levels with fewer work-groups than this (clusters x column slabs) take 16-column slabs:
-// more work-groups with half the work each shorten a level that is one wave of work-groups
-constexpr int64_t kNarrowLevel = 256;
 // forward leaf transform for k <= 32 with V_t^T straight into the matrix-core registers
 constexpr bool kSmallFwdLeaf = true;
 
@@ -477,50 +470,14 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
         }
     };
     auto up_levels = [&](int dhi, int dlo) {  // upward levels dhi down to dlo
-        for (int d = dhi; d >= dlo; --d) {
-            const int32_t b = P.lvl_inner_ptr[d], e = P.lvl_inner_ptr[d + 1];
-            if (e <= b) continue;
-            if (inter)
-                level_near(true, b, e);
-            else if (t64 && kKronTransfer && NJ > 1 && (int64_t)(e - b) * gy < kNarrowLevel)
-                hipLaunchKernelGGL((kron::k_up<4, 16>), dim3(e - b, (unsigned)((m + 15) / 16)), dim3(256), 0, st, m,
-                                   dm.lvl_inner + b, dm.up_son + 2 * b, dm.E1, xh, ldh, sk);
-            else if (t64 && kKronTransfer)
-                hipLaunchKernelGGL((kron::k_up<4, 16 * NJ>), dim3(e - b, gy), dim3(256), 0, st, m, dm.lvl_inner + b,
-                                   dm.up_son + 2 * b, dm.E1, xh, ldh, sk);
-            else if (t64)
-                hipLaunchKernelGGL(mfma::k_up64<NJ>, dim3(e - b, gy), dim3(256), 0, st, m, dm.lvl_inner + b,
-                                   dm.up_son + 2 * b, E, xh, ldh, sk);
-            else if (dm.p == 3 && kKronTransfer)
-                hipLaunchKernelGGL((kron::k_up<3, 16 * NJ>), dim3(e - b, gy), dim3(256), 0, st, m, dm.lvl_inner + b,
-                                   dm.up_son + 2 * b, dm.E1, xh, ldh, sk);
-            else
-                hipLaunchKernelGGL(mfma::k_up<NJ>, dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_inner + b,
-                                   dm.up_son + 2 * b, E, xh, ldh, sk);
-        }
+        if (!inter) return kron::up_levels_p<NJ>(dm, m, dhi, dlo, xh, ldh, st, sk);
+        for (int d = dhi; d >= dlo; --d)
+            if (P.lvl_inner_ptr[d + 1] > P.lvl_inner_ptr[d]) level_near(true, P.lvl_inner_ptr[d], P.lvl_inner_ptr[d + 1]);
     };
     auto down_levels = [&](int dlo, int dhi) {  // downward levels (son depths) dlo up to dhi
-        for (int d = dlo; d <= dhi; ++d) {
-            const int32_t b = P.lvl_ptr[d], e = P.lvl_ptr[d + 1];
-            if (e <= b) continue;
-            if (inter)
-                level_near(false, b, e);
-            else if (t64 && kKronTransfer && NJ > 1 && (int64_t)(e - b) * gy < kNarrowLevel)
-                hipLaunchKernelGGL((kron::k_down<4, 16>), dim3(e - b, (unsigned)((m + 15) / 16)), dim3(256), 0, st, m,
-                                   dm.lvl_all + b, dm.dn_par + b, dm.E1, yh, ldh, sk);
-            else if (t64 && kKronTransfer)
-                hipLaunchKernelGGL((kron::k_down<4, 16 * NJ>), dim3(e - b, gy), dim3(256), 0, st, m, dm.lvl_all + b,
-                                   dm.dn_par + b, dm.E1, yh, ldh, sk);
-            else if (t64)
-                hipLaunchKernelGGL(mfma::k_down64<NJ>, dim3(e - b, gy), dim3(256), 0, st, m, dm.lvl_all + b,
-                                   dm.dn_par + b, E, yh, ldh, sk);
-            else if (dm.p == 3 && kKronTransfer)
-                hipLaunchKernelGGL((kron::k_down<3, 16 * NJ>), dim3(e - b, gy), dim3(256), 0, st, m, dm.lvl_all + b,
-                                   dm.dn_par + b, dm.E1, yh, ldh, sk);
-            else
-                hipLaunchKernelGGL(mfma::k_down<NJ>, dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_all + b,
-                                   dm.dn_par + b, E, yh, ldh, sk);
-        }
+        if (!inter) return kron::down_levels_p<NJ>(dm, m, dlo, dhi, yh, ldh, st, sk);
+        for (int d = dlo; d <= dhi; ++d)
+            if (P.lvl_ptr[d + 1] > P.lvl_ptr[d]) level_near(false, P.lvl_ptr[d], P.lvl_ptr[d + 1]);
     };
     // complex operator: y-hat += S_im (J x-hat), so that y-hat = (S_re + i S_im) x-hat per complex column
     auto coupling = [&](hipStream_t s, int32_t nrows, const int32_t *rows, size_t keep) {
@@ -538,8 +495,7 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
             int dev = 0, per_cu = 0;
             const void *fl = NP == 2 ? (const void *)mfma::k_leaf_cat<2> : (const void *)mfma::k_leaf_cat<1>;
             if (hipFuncGetAttributes(&fa, fl) == hipSuccess &&
-                hipFuncGetAttributes(&fu, kKronTransfer ? (const void *)kron::k_up<4, 16 * NJ>
-                                                        : (const void *)mfma::k_up64<NJ>) == hipSuccess &&
+                hipFuncGetAttributes(&fu, (const void *)kron::k_up<4, 16 * NJ>) == hipSuccess &&
                 hipGetDevice(&dev) == hipSuccess &&
                 hipDeviceGetAttribute(&per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) ==
                     hipSuccess) {
@@ -586,12 +542,8 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
         size_t keep = 0;
         if (cfg.split == 1) {
             hipFuncAttributes a{}, b{};
-            const void *fu = t64 ? (kKronTransfer ? (const void *)kron::k_up<4, 16 * NJ> : (const void *)mfma::k_up64<NJ>)
-                             : (dm.p == 3 && kKronTransfer ? (const void *)kron::k_up<3, 16 * NJ>
-                                                           : (const void *)mfma::k_up<NJ>);
-            const void *fd = t64 ? (kKronTransfer ? (const void *)kron::k_down<4, 16 * NJ> : (const void *)mfma::k_down64<NJ>)
-                             : (dm.p == 3 && kKronTransfer ? (const void *)kron::k_down<3, 16 * NJ>
-                                                           : (const void *)mfma::k_down<NJ>);
+            const void *fu = t64 ? (const void *)kron::k_up<4, 16 * NJ> : (const void *)kron::k_up<3, 16 * NJ>;
+            const void *fd = t64 ? (const void *)kron::k_down<4, 16 * NJ> : (const void *)kron::k_down<3, 16 * NJ>;
             if (hipFuncGetAttributes(&a, fu) == hipSuccess && hipFuncGetAttributes(&b, fd) == hipSuccess)
                 keep = std::max(a.sharedSizeBytes, b.sharedSizeBytes);
         }
@@ -639,44 +591,7 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     if (ev) (void)hipEventRecord(ev[6], st);
 }
 
-// Transfer levels and forward leaf transform of the ranks above 64 (p = 5 to 8): 16-column slabs
-// (the Kronecker passes hold both sons' k rows in LDS: 139 KB at p = 8)
-void gen_up_levels(const DevMat &dm, int64_t m, double *xh, int64_t ldh, hipStream_t st, Skip sk) {
-    const Plan &P = *dm.plan;
-    for (int d = dm.depth_max - 1; d >= P.adm_depth; --d) {
-        const int32_t b = P.lvl_inner_ptr[d], e = P.lvl_inner_ptr[d + 1];
-        if (e <= b) continue;
-        auto go = [&](auto Pc) {
-            hipLaunchKernelGGL((kron::k_up<decltype(Pc)::value, 16>), dim3(e - b, (unsigned)((m + 15) / 16)), dim3(256),
-                               0, st, m, dm.lvl_inner + b, dm.up_son + 2 * b, dm.E1, xh, ldh, sk);
-        };
-        switch (dm.p) {
-            case 5: go(std::integral_constant<int, 5>{}); break;
-            case 6: go(std::integral_constant<int, 6>{}); break;
-            case 7: go(std::integral_constant<int, 7>{}); break;
-            default: go(std::integral_constant<int, 8>{}); break;
-        }
-    }
-}
-
-void gen_down_levels(const DevMat &dm, int64_t m, double *yh, int64_t ldh, hipStream_t st, Skip sk) {
-    const Plan &P = *dm.plan;
-    for (int d = std::max(1, P.adm_depth + 1); d <= dm.depth_max; ++d) {
-        const int32_t b = P.lvl_ptr[d], e = P.lvl_ptr[d + 1];
-        if (e <= b) continue;
-        auto go = [&](auto Pc) {
-            hipLaunchKernelGGL((kron::k_down<decltype(Pc)::value, 16>), dim3(e - b, (unsigned)((m + 15) / 16)),
-                               dim3(256), 0, st, m, dm.lvl_all + b, dm.dn_par + b, dm.E1, yh, ldh, sk);
-        };
-        switch (dm.p) {
-            case 5: go(std::integral_constant<int, 5>{}); break;
-            case 6: go(std::integral_constant<int, 6>{}); break;
-            case 7: go(std::integral_constant<int, 7>{}); break;
-            default: go(std::integral_constant<int, 8>{}); break;
-        }
-    }
-}
-
+// forward leaf transform of the ranks above 64
 void gen_fwd_leaf(const DevMat &dm, int64_t m, const double *Xt, int64_t ldxt, double *xh, int64_t ldh, hipStream_t st,
                   Skip sk) {
     const int nj = (int)std::min<int64_t>(4, (m + 15) / 16);
@@ -708,17 +623,18 @@ const double *tree_rows(const DevMat &dm, int64_t m, const double *X, int64_t &l
 void matmul_gen_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alpha, const double *X, int64_t ldx,
                     double beta, double *Y, int64_t ldy, int to, double *xh, double *yh, int64_t ldh, double *xt_ws,
                     hipStream_t st, const std::function<void(int)> &mark, hipEvent_t *ev, const int32_t *skip) {
+    const Plan &P = *dm.plan;
     const Skip sk{skip, dm.sys_of};
     mark(0);
     int64_t ldxt = ldx;
     const double *Xt = tree_rows(dm, m, X, ldxt, to, xt_ws, st);
     gen_fwd_leaf(dm, m, Xt, ldxt, xh, ldh, st, sk);
     mark(1);
-    gen_up_levels(dm, m, xh, ldh, st, sk);
+    kron::up_levels_p<1>(dm, m, dm.depth_max - 1, P.adm_depth, xh, ldh, st, sk);
     mark(2);
     launch_coupling_rows(dm, m, xh, yh, ldh, st, sk, cfg.nj_coupling);
     mark(3);
-    gen_down_levels(dm, m, yh, ldh, st, sk);
+    kron::down_levels_p<1>(dm, m, std::max(1, P.adm_depth + 1), dm.depth_max, yh, ldh, st, sk);
     mark(4);
     const int NP = cfg.np_leaf ? cfg.np_leaf : (m > 32 ? 2 : 1);
     const size_t cat_lds = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
@@ -914,7 +830,7 @@ hipError_t matmul_lp(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
 hipError_t run_forward_transform(const DevMat &dm, int64_t m, const double *X, int64_t ldx, bool tree_order,
                                  double *xh, int64_t ldh, double *xt_ws, hipStream_t st) {
     const Plan &P = *dm.plan;
-    const double *V = (const double *)dm.V, *E = (const double *)dm.E;
+    const double *V = (const double *)dm.V;
     if (dm.mc) {
         const double *Xt = X;
         int64_t ldxt = ldx;
@@ -931,18 +847,7 @@ hipError_t run_forward_transform(const DevMat &dm, int64_t m, const double *X, i
             constexpr int NJ = decltype(NJc)::value;
             hipLaunchKernelGGL(mfma::k_fwd_leaf<NJ>, dim3(dm.L, gy), dim3(256), 0, st, dm.k, m, dm.leaves, dm.first,
                                dm.size, dm.perm, V, Xt, ldxt, 1, xh, ldh, Skip{});
-            for (int d = dm.depth_max - 1; d >= P.adm_depth; --d) {
-                const int32_t b = P.lvl_inner_ptr[d], e = P.lvl_inner_ptr[d + 1];
-                if (e > b && dm.k == 64 && kKronTransfer)
-                    hipLaunchKernelGGL((kron::k_up<4, 16 * NJ>), dim3(e - b, gy), dim3(256), 0, st, m, dm.lvl_inner + b,
-                                       dm.up_son + 2 * b, dm.E1, xh, ldh, Skip{});
-                else if (e > b && dm.p == 3 && kKronTransfer)
-                    hipLaunchKernelGGL((kron::k_up<3, 16 * NJ>), dim3(e - b, gy), dim3(256), 0, st, m, dm.lvl_inner + b,
-                                       dm.up_son + 2 * b, dm.E1, xh, ldh, Skip{});
-                else if (e > b)
-                    hipLaunchKernelGGL(mfma::k_up<NJ>, dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_inner + b,
-                                       dm.up_son + 2 * b, E, xh, ldh, Skip{});
-            }
+            kron::up_levels_p<NJ>(dm, m, dm.depth_max - 1, P.adm_depth, xh, ldh, st, Skip{});
         };
         switch (nj) {
             case 1: launch(std::integral_constant<int, 1>{}); break;
@@ -957,24 +862,11 @@ hipError_t run_forward_transform(const DevMat &dm, int64_t m, const double *X, i
 
 hipError_t run_down_pass(const DevMat &dm, int64_t m, double *yh, int64_t ldh, hipStream_t st) {
     const Plan &P = *dm.plan;
-    const double *E = (const double *)dm.E;
     if (dm.mc) {
         const int nj = (int)std::min<int64_t>(4, (m + 15) / 16);
-        const unsigned gy = (unsigned)((m + 16 * nj - 1) / (16 * nj));
         auto go = [&](auto NJc) {
             constexpr int NJ = decltype(NJc)::value;
-            for (int d = std::max(1, P.adm_depth + 1); d <= dm.depth_max; ++d) {
-                const int32_t b = P.lvl_ptr[d], e = P.lvl_ptr[d + 1];
-                if (e > b && dm.k == 64 && kKronTransfer)
-                    hipLaunchKernelGGL((kron::k_down<4, 16 * NJ>), dim3(e - b, gy), dim3(256), 0, st, m, dm.lvl_all + b,
-                                       dm.dn_par + b, dm.E1, yh, ldh, Skip{});
-                else if (e > b && dm.p == 3 && kKronTransfer)
-                    hipLaunchKernelGGL((kron::k_down<3, 16 * NJ>), dim3(e - b, gy), dim3(256), 0, st, m, dm.lvl_all + b,
-                                       dm.dn_par + b, dm.E1, yh, ldh, Skip{});
-                else if (e > b)
-                    hipLaunchKernelGGL(mfma::k_down<NJ>, dim3(e - b, gy), dim3(256), 0, st, dm.k, m, dm.lvl_all + b,
-                                       dm.dn_par + b, E, yh, ldh, Skip{});
-            }
+            kron::down_levels_p<NJ>(dm, m, std::max(1, P.adm_depth + 1), dm.depth_max, yh, ldh, st, Skip{});
         };
         switch (nj) {
             case 1: go(std::integral_constant<int, 1>{}); break;

@@ -194,43 +194,6 @@ __global__ __launch_bounds__(256) void k_fwd_leaf(int k, int64_t m, const int32_
                 if (out_row(r) < k) xh[((int64_t)t * k + out_row(r)) * ldh + j0 + out_col(J)] = acc[J][r];
 }
 
-// x_t = E_{t0}^T x_{t0} + E_{t1}^T x_{t1} for the inner clusters in `list`;
-// son[2 i], son[2 i + 1] are the sons of list[i].  Both terms are loaded at once.
-template <int NJ>
-__global__ __launch_bounds__(256) void k_up(int k, int64_t m, const int32_t *__restrict__ list,
-                                            const int32_t *__restrict__ son, const double *__restrict__ E,
-                                            double *__restrict__ xh, int64_t ldh, Skip skip) {
-    __shared__ Smem<NJ> sm;
-    const int32_t t = list[blockIdx.x], s0 = son[2 * blockIdx.x], s1 = son[2 * blockIdx.x + 1];
-    if (skip(t)) return;
-    const int64_t j0 = (int64_t)blockIdx.y * Smem<NJ>::MC;
-    const int mc = (int)min<int64_t>(Smem<NJ>::MC, m - j0);
-    auto term = [&](int32_t sn) {
-        return Term{E + (int64_t)sn * k * k, k, k, k, true, xh + j0, ldh, nullptr, (int64_t)sn * k};
-    };
-    const Term d0 = term(s0), d1 = term(s1);
-    Regs<NJ> R0, R1;
-    load_term<NJ>(d0, mc, R0);
-    load_term<NJ>(d1, mc, R1);
-    if (k < K) clear<NJ>(sm);  // padding rows and columns of the k x k tiles
-    dbl4 acc[NJ];
-    zero<NJ>(acc);
-    const int kp = dkpad4(k);
-    store_term<NJ>(d0, mc, R0, sm);
-    __syncthreads();
-    mma<NJ>(sm.a, sm.b, kp, k, acc);
-    __syncthreads();
-    store_term<NJ>(d1, mc, R1, sm);
-    __syncthreads();
-    mma<NJ>(sm.a, sm.b, kp, k, acc);
-#pragma unroll
-    for (int J = 0; J < NJ; ++J)
-        if (out_col(J) < mc)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (out_row(r) < k) xh[((int64_t)t * k + out_row(r)) * ldh + j0 + out_col(J)] = acc[J][r];
-}
-
 // Forward leaf transform and upward transfer pass in one launch: the work-group
 // of leaf t computes x_t = V_t^T X|_t, then walks up the tree.  At each parent
 // the work-group that finishes second (a device-scope counter per parent and
@@ -299,40 +262,13 @@ static __global__ void k_zero_i32(int64_t count, int32_t *__restrict__ p) {
     if (e < count) p[e] = 0;
 }
 
-// y_c += E_c y_parent(c) for the clusters in `list`; par[i] is the parent of list[i]
-template <int NJ>
-__global__ __launch_bounds__(256) void k_down(int k, int64_t m, const int32_t *__restrict__ list,
-                                              const int32_t *__restrict__ par, const double *__restrict__ E,
-                                              double *__restrict__ yh, int64_t ldh, Skip skip) {
-    __shared__ Smem<NJ> sm;
-    const int32_t c = list[blockIdx.x], p = par[blockIdx.x];
-    if (skip(c)) return;
-    const int64_t j0 = (int64_t)blockIdx.y * Smem<NJ>::MC;
-    const int mc = (int)min<int64_t>(Smem<NJ>::MC, m - j0);
-    const Term d{E + (int64_t)c * k * k, k, k, k, false, yh + j0, ldh, nullptr, (int64_t)p * k};
-    Regs<NJ> R;
-    load_term<NJ>(d, mc, R);
-    if (k < K) clear<NJ>(sm);  // padding rows and columns of the k x k tile
-    dbl4 acc[NJ];
-    zero<NJ>(acc);
-    store_term<NJ>(d, mc, R, sm);
-    __syncthreads();
-    mma<NJ>(sm.a, sm.b, dkpad4(k), k, acc);
-#pragma unroll
-    for (int J = 0; J < NJ; ++J)
-        if (out_col(J) < mc)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (out_row(r) < k) yh[((int64_t)c * k + out_row(r)) * ldh + j0 + out_col(J)] += acc[J][r];
-}
-
 // Transfer passes for rank k = 64 with the transfer matrices straight from memory as the
 // matrix-core left operand: wave w holds rows 16w..16w+15 of E_s^T (upward) or E_s
 // (downward) in registers, 16 k-steps of one 8-byte load per lane (upward: 16 lanes over
 // 16 consecutive entries of a row of E_s; downward: 16 rows of E_s, their 128-byte lines
 // shared by four k-steps through the L1), so that only the right operand (x-hat or y-hat
 // rows, 64 x 16*NJ) goes through LDS, both upward terms at once behind one barrier.  The
-// k-steps and terms are summed in the order of k_up / k_down.
+// k-steps and terms are summed in ascending order.
 //   upward:   x_t = E_{s0}^T x_{s0} + E_{s1}^T x_{s1}   (list, son as for k_up)
 //   downward: y_c += E_c y_{par(c)}                    (list, par as for k_down)
 // by: the column slab; bs: NT x 64 x (16 NJ + 1) doubles of LDS
@@ -414,22 +350,6 @@ __device__ inline void down64_item(int i, int by, int64_t m, const int32_t *__re
         if (out_col(J) < mc)
 #pragma unroll
             for (int r = 0; r < 4; ++r) yh[((int64_t)c * 64 + out_row(r)) * ldh + j0 + out_col(J)] += acc[J][r];
-}
-
-template <int NJ>
-__global__ __launch_bounds__(256) void k_up64(int64_t m, const int32_t *__restrict__ list,
-                                              const int32_t *__restrict__ son, const double *__restrict__ E,
-                                              double *__restrict__ xh, int64_t ldh, Skip skip) {
-    __shared__ double bs[2 * 64 * (16 * NJ + 1)];
-    up64_item<NJ>(blockIdx.x, blockIdx.y, m, list, son, E, xh, ldh, skip, bs);
-}
-
-template <int NJ>
-__global__ __launch_bounds__(256) void k_down64(int64_t m, const int32_t *__restrict__ list,
-                                                const int32_t *__restrict__ par, const double *__restrict__ E,
-                                                double *__restrict__ yh, int64_t ldh, Skip skip) {
-    __shared__ double bs[64 * (16 * NJ + 1)];
-    down64_item<NJ>(blockIdx.x, blockIdx.y, m, list, par, E, yh, ldh, skip, bs);
 }
 
 // Forward leaf transform for rank 64, x_t = V_t^T X|_t, with V_t^T straight into the
