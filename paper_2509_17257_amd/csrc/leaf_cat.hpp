@@ -102,7 +102,8 @@ constexpr size_t leaf_cat_red_bytes() { return sizeof(double) * 64 * (32 * NP + 
 // eighth (taken in the order of a.order: the most work first); the slabs of one leaf are
 // consecutive slots of one XCD, so its near blocks come from HBM once.  red: 64 x (32 NP + 1) doubles of LDS; xrow: the near-row table.
 template <int NP>
-__device__ inline void leaf_cat_slot(int64_t slot, const LeafCatArgs &a, double *red, int32_t *xrow) {
+__device__ inline void leaf_cat_slot(int64_t slot, const LeafCatArgs &a, double *red) {
+    int32_t *xrow = (int32_t *)red;
     constexpr int MC = 32 * NP, LDR = MC + 1;
     const int32_t per_xcd = (a.L + 7) / 8;
     const int nslab = (int)((a.m + MC - 1) / MC);
@@ -121,13 +122,14 @@ __device__ inline void leaf_cat_slot(int64_t slot, const LeafCatArgs &a, double 
     const int mc = (int)min<int64_t>(MC, a.m - j0);
     const int64_t q0 = a.near_ptr[l];
     const int nnear = a.near ? (int)(a.near_ptr[l + 1] - q0) : 0;
-    const int32_t rn = nnear > 0 ? cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size) : 0;
     const double *nb = nnear > 0 ? a.Nt + a.near_off[q0] : a.Nt;
     const double *vb = a.Vt + a.vt_off[l];
-    const int RN = (rn + 15) >> 4, RB = a.basis ? (k + 15) >> 4 : 0, RT = RN + RB;
     const int xc = (mc - 1) & ~1;  // last even column offset of the slab
 
     for (int i0 = 0; i0 < nt; i0 += 64) {
+        const int32_t rn =
+            nnear > 0 ? cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size) : 0;
+        const int RN = (rn + 15) >> 4, RB = a.basis ? (k + 15) >> 4 : 0, RT = RN + RB;
         const int ic = min(64, nt - i0);
         const int ntile = (ic + 15) >> 4;
         if (NP == 2 && ntile == 3) {
@@ -190,6 +192,7 @@ __device__ inline void leaf_cat_slot(int64_t slot, const LeafCatArgs &a, double 
                     if (r > last) break;
                 }
             }
+            __syncthreads();  // the row table is read for the last time: its LDS takes the partial tiles
             for (int gg = 0; gg < 2; ++gg) {
                 if (g == gg)
 #pragma unroll
@@ -290,6 +293,7 @@ __device__ inline void leaf_cat_slot(int64_t slot, const LeafCatArgs &a, double 
                     if (r > last) break;
                 }
             }
+            __syncthreads();  // the row table is read for the last time: its LDS takes the partial tiles
             // partial tiles of the G waves of each row group, added in wave order.  Lane l,
             // register q of acc[2p + hj][I] -> column 32p + 2 (l / 16 + 4 q) + hj, row
             // 16 (tl0 + I) + l % 16.
@@ -494,9 +498,8 @@ __global__ __launch_bounds__(256, 2) void k_dell_near(LeafCatArgs a, DellArgs d,
 // the leaf stage over slots [slot0, slot1): dynamic LDS = the near-row table
 template <int NP>
 __global__ __launch_bounds__(256, NP == 1 ? 3 : 2) void k_leaf_cat(LeafCatArgs a, int64_t slot0, int64_t slot1) {
-    __shared__ double red[64 * (32 * NP + 1)];
-    extern __shared__ int32_t xrow[];
-    for (int64_t slot = slot0 + blockIdx.x; slot < slot1; slot += gridDim.x) leaf_cat_slot<NP>(slot, a, red, xrow);
+    extern __shared__ double red[];
+    for (int64_t slot = slot0 + blockIdx.x; slot < slot1; slot += gridDim.x) leaf_cat_slot<NP>(slot, a, red);
 }
 
 // A transfer level with a share of the near field beside it: work-groups [0, items) run the
@@ -520,7 +523,7 @@ __global__ __launch_bounds__(256, 2) void k_level_near(int64_t items, int gy, in
         else
             down64_item<NJ>(i, by, m, list, aux, E, hat, ldh, skip, lds);
     } else if (b >= items + lead) {
-        leaf_cat_slot<NP>(slot0 + (b - items - lead), a, lds, (int32_t *)(lds + 64 * (32 * NP + 1)));
+        leaf_cat_slot<NP>(slot0 + (b - items - lead), a, lds);
     }
 }
 

@@ -10,10 +10,22 @@
 // (both factors of a product in the storage type).  Only the end of each segment is padded (to
 // 16 rows) and the rows of the leaf come in 16-row tiles.
 //
+// Work-group: two or four waves for one (leaf, slab of 16 NC columns).  Two waves each take every
+// second round for all row tiles of a 64-row chunk and all column tiles, so every operand is loaded
+// once per work-group; four waves split chunks above 32 rows into two row groups (each loads the
+// rows of X for itself), so that few leaves still fill the chip.  The sums are the same bit for
+// bit.  Bound by the FP32 matrix cores (65 % busy) and the loads that feed them.  Slabs of 32 or
+// 64 columns spent up to a quarter of the products on padding and row groups 22 GB of cache
+// traffic where 13 do: 45 columns, n = 99991, BF16 basis, leaf stage 1029 -> 790 us; 64 columns,
+// n = 262144, FP32 2330 -> 2150 us.  Registers allow two waves per SIMD and one round of
+// loads ahead; two rounds ahead spill (5 x slower), half rounds three ahead are 1 % slower.  The
+// row table and the partial tiles take the same LDS (beside each other: + 8 % of a product with
+// tables of 30 KB).
+//
 // Lane layout of v_mfma_f32_16x16x4f32 (A: 16 x 4, B: 4 x 16, D: 16 x 16): lane l holds
 // A[l % 16][l / 16], B[l / 16][l % 16] and D rows 4 (l / 16) + q, column l % 16 (q = 0..3).
-// Here A = X^T (a lane loads two neighbouring columns with one 8-byte load, which feed an
-// "even" and an "odd" column tile) and B = N^T (one 4-byte load per row tile and k-step).
+// Here A = X^T and B = N^T: a lane loads two neighbouring columns (rows) with one 8-byte load,
+// which feed an "even" and an "odd" tile; an odd last tile is loaded by 4 bytes per lane.
 #pragma once
 
 #include "leaf_cat.hpp"
@@ -22,11 +34,12 @@
 namespace h2x {
 namespace lp {
 
-template <int NP>
+template <int NC, int NT>
 struct CatRoundLp {
-    flt2 a[NP][4];  // [column half p][k-step u]: columns 32p + 2 (l % 16) + {0, 1}
-    float b[2][4];  // [row tile of the wave][k-step u]: row 16 I + l % 16
-    int ok[4];      // k-row of step u inside its segment
+    flt2 a[NC / 2 + 1][4];  // [column pair p][k-step u]: columns 32p + 2 (l % 16) + {0, 1}
+    float c[4];             // [k-step u], NC odd: column 16 (NC - 1) + l % 16
+    flt2 b[NT / 2][4];      // [row pair q][k-step u]: rows 32q + 2 (l % 16) + {0, 1}
+    float d[4];             // [k-step u], NT odd: row 16 (NT - 1) + l % 16
 };
 
 __device__ inline float ld1(const float *p) { return *p; }
@@ -55,17 +68,138 @@ struct LeafCatLpArgs {
     Skip skip;
 };
 
-template <int NP>
-constexpr size_t leaf_cat_lp_red_bytes() { return sizeof(float) * 64 * (32 * NP + 1); }
+template <int NC>
+constexpr size_t leaf_cat_lp_red_bytes() { return sizeof(float) * 64 * (16 * NC + 1); }
+
+// NT row tiles from row i0 on (ic of these rows present) and NC column tiles.  The rounds are summed
+// in G groups (group r % G: two where the chunk has three or four row tiles, four below); of the GW
+// waves of these rows, wave g takes the groups g, g + GW, .. in turn.  The groups' partial tiles
+// are added in LDS in order (red: their first row).
+template <int NC, int NT, int G, int GW, typename TV>
+__device__ inline void leaf_cat_lp_chunk(const LeafCatLpArgs &a, int g, int lr, int lq, int32_t t, const float *nb,
+                                         const TV *vb, int32_t rn, int64_t nt2, int i0, int ic, int64_t j0, int xc,
+                                         const int32_t *xrow, float *red) {
+    constexpr int NA = G / GW, LDR = 16 * NC + 1, NPR = NC / 2;
+    const int k = a.k;
+    const int RN = (rn + 15) >> 4, RT = RN + ((k + 15) >> 4);
+    // (row lengths are even: a pair stays inside its row)
+    uint32_t row[NT / 2];
+#pragma unroll
+    for (int q = 0; q < NT / 2; ++q) row[q] = (uint32_t)(i0 + min(32 * q + 2 * lr, (ic - 1) & ~1));
+    const uint32_t rs = (uint32_t)(i0 + min(16 * (NT - 1) + lr, ic - 1));
+    uint32_t cp[NPR + 1];
+#pragma unroll
+    for (int p = 0; p < NPR; ++p) cp[p] = (uint32_t)min(32 * p + 2 * lr, xc);
+    const uint32_t cs = (uint32_t)min(16 * (NC - 1) + lr, xc + 1);
+
+    flt4v acc[NA][NC][NT];
+#pragma unroll
+    for (int x = 0; x < NA; ++x)
+#pragma unroll
+        for (int J = 0; J < NC; ++J)
+#pragma unroll
+            for (int I = 0; I < NT; ++I) acc[x][J][I] = flt4v{0.f, 0.f, 0.f, 0.f};
+
+    // round r -> registers; both branches issue the same number of loads from clamped in-range
+    // addresses, so the wait counts stay exact.  The near-field operands come through buffer
+    // resources (32-bit byte offsets; the host takes this form only while X is below 4 GiB).
+    auto load = [&](int r, CatRoundLp<NC, NT> &R) {
+        if (r < RN) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int cc = min(16 * r + 4 * u + lq, rn - 1);
+                const __amdgpu_buffer_rsrc_t rx = buf_rsrc(a.Xt + j0, 0xFFFFFFFFu), rb = buf_rsrc(nb, 0xFFFFFFFFu);
+                const uint32_t xo = (uint32_t)(xrow[cc] * a.ldxt), bo = (uint32_t)(cc * nt2);
+#pragma unroll
+                for (int p = 0; p < NPR; ++p) R.a[p][u] = __builtin_bit_cast(flt2, buf_ld8<0>(rx, 4u * (xo + cp[p])));
+                if (NC & 1) R.c[u] = buf_ld4f<0>(rx, 4u * (xo + cs));
+#pragma unroll
+                for (int q = 0; q < NT / 2; ++q)
+                    R.b[q][u] = __builtin_bit_cast(flt2, buf_ld8<0>(rb, 4u * (bo + row[q])));
+                if (NT & 1) R.d[u] = buf_ld4f<0>(rb, 4u * (bo + rs));
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int cc = min(16 * (r - RN) + 4 * u + lq, k - 1);
+                const float *ar = a.yh + ((int64_t)t * k + cc) * a.ldh + j0;
+#pragma unroll
+                for (int p = 0; p < NPR; ++p) R.a[p][u] = ld2(ar + cp[p]);
+                if (NC & 1) R.c[u] = ar[cs];
+#pragma unroll
+                for (int q = 0; q < NT / 2; ++q) R.b[q][u] = ld2(vb + (int64_t)cc * nt2 + row[q]);
+                if (NT & 1) R.d[u] = ld1(vb + (int64_t)cc * nt2 + rs);
+            }
+        }
+    };
+    // the products of round r; rows past its segment are zeroed here
+    auto multiply = [&](int r, const CatRoundLp<NC, NT> &R, flt4v(&ac)[NC][NT]) {
+        const bool basis = r >= RN, rnd = a.round_y && basis;
+        const int rem = basis ? k - 16 * (r - RN) : rn - 16 * r;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool ok = 4 * u + lq < rem;
+#pragma unroll
+            for (int J = 0; J < NC; ++J) {
+                float v = ((NC & 1) && J == NC - 1) ? R.c[u] : R.a[J >> 1][u][J & 1];
+                v = ok ? v : 0.f;
+                if (rnd) v = round_bf16(v);
+#pragma unroll
+                for (int I = 0; I < NT; ++I)
+                    ac[J][I] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        v, ((NT & 1) && I == NT - 1) ? R.d[u] : R.b[I >> 1][u][I & 1], ac[J][I], 0, 0, 0);
+            }
+        }
+    };
+
+    if (g < RT) {
+        const int last = g + ((RT - 1 - g) / GW) * GW;  // the wave's last round
+        CatRoundLp<NC, NT> s0, s1;
+        int r = g;
+        load(r, s0);
+        // two register sets in turn, loaded one round ahead of their use (a round past the last
+        // re-reads that one, which the cache serves)
+        for (;;) {
+            load(min(r + GW, last), s1);
+            multiply(r, s0, acc[0]);
+            if ((r += GW) > last) break;
+            load(min(r + GW, last), s0);
+            multiply(r, s1, acc[NA - 1]);
+            if ((r += GW) > last) break;
+        }
+    }
+    __syncthreads();  // the row table was read for the last time: its LDS takes the partial tiles
+    // Lane l, register q of a pair tile J -> column 32 (J / 2) + 2 (4 (l / 16) + q) + J % 2, of a
+    // single last tile -> column 16 (NC - 1) + 4 (l / 16) + q; rows as in the loads.
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+        if (g == gg % GW)
+#pragma unroll
+            for (int J = 0; J < NC; ++J)
+#pragma unroll
+                for (int I = 0; I < NT; ++I) {
+                    const int row = ((NT & 1) && I == NT - 1) ? 16 * I + lr : 32 * (I >> 1) + 2 * lr + (I & 1);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int col = ((NC & 1) && J == NC - 1) ? 16 * J + 4 * lq + q
+                                                                  : 32 * (J >> 1) + 2 * (4 * lq + q) + (J & 1);
+                        float *cell = &red[row * LDR + col];
+                        const float v = acc[gg / GW][J][I][q];
+                        *cell = (gg == 0) ? v : *cell + v;
+                    }
+                }
+        __syncthreads();
+    }
+}
 
 // one (leaf, column slab) per work-group, mapped to XCDs as in the FP64 form (slot & 7 is the
 // XCD, whose leaves form one contiguous eighth of the launch order; the slabs of one leaf are
-// consecutive slots of one XCD).  Dynamic LDS: the near-row table.
-template <int NP, typename TV>
-__global__ __launch_bounds__(256, 2) void k_leaf_cat_lp(LeafCatLpArgs a) {
-    constexpr int MC = 32 * NP, LDR = MC + 1;
-    __shared__ float red[64 * LDR];
-    extern __shared__ int32_t xrow[];
+// consecutive slots of one XCD).  Dynamic LDS: the near-row table, then the partial tiles.
+template <int NC, int NW, typename TV>
+__global__ __launch_bounds__(64 * NW, 2) void k_leaf_cat_lp(LeafCatLpArgs a) {
+    constexpr int MC = 16 * NC, LDR = MC + 1;
+    extern __shared__ float red[];
+    int32_t *xrow = (int32_t *)red;
     const int64_t slot = blockIdx.x;
     const int32_t per_xcd = (a.L + 7) / 8;
     const int nslab = (int)((a.m + MC - 1) / MC);
@@ -77,130 +211,29 @@ __global__ __launch_bounds__(256, 2) void k_leaf_cat_lp(LeafCatLpArgs a) {
     const int32_t l = a.order[pos];
     const int32_t t = a.leaves[l];
     if (a.skip(t)) return;
-    const int k = a.k;
     const int nt = a.size[t];
     const int64_t nt2 = pad_rows(nt), r0 = a.first[t];
     const int64_t j0 = (qx % nslab) * MC;
     const int mc = (int)min<int64_t>(MC, a.m - j0);
     const int64_t q0 = a.near_ptr[l];
     const int nnear = (int)(a.near_ptr[l + 1] - q0);
-    const int32_t rn =
-        nnear > 0 ? mfma::cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size) : 0;
     const float *nb = nnear > 0 ? a.Nt + a.near_off[q0] : a.Nt;
     const TV *vb = (const TV *)a.Vt + a.vt_off[l];
-    const int RN = (rn + 15) >> 4, RT = RN + ((k + 15) >> 4);
     const int xc = (mc - 1) & ~1;  // last even column offset of the slab
-    // two row tiles per wave: a 64-row chunk of more than two tiles is two row groups of two
-    // waves (k-groups), otherwise one row group of all four waves
     for (int i0 = 0; i0 < nt; i0 += 64) {
+        const int32_t rn =
+            nnear > 0 ? mfma::cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size) : 0;
         const int ic = min(64, nt - i0);
-        const int ntile = (ic + 15) >> 4;
-        const int G = ntile > 2 ? 2 : 4;       // waves per row group (k-groups)
-        const int wr = w / G, g = w - wr * G;  // row group, k-group (wave-uniform)
-        const int tl0 = 2 * wr;                // first row tile of the wave
-        const bool t0 = tl0 < ntile, t1 = tl0 + 1 < ntile;
-        const int row_a = i0 + min(16 * tl0 + lr, ic - 1), row_b = i0 + min(16 * tl0 + 16 + lr, ic - 1);
-
-        flt4v acc[2 * NP][2];
-#pragma unroll
-        for (int J = 0; J < 2 * NP; ++J) acc[J][0] = acc[J][1] = flt4v{0.f, 0.f, 0.f, 0.f};
-
-        // round r (clamped to the wave's rounds) -> registers; both branches issue the same
-        // number of loads from clamped in-range addresses, so the wait counts stay exact.  The
-        // near-field operands come through buffer resources (32-bit byte offsets; the host
-        // takes this form only while X is below 4 GiB).
-        auto load = [&](int r, CatRoundLp<NP> &R) {
-            if (r < RN) {
-                const int c0 = 16 * r;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int c = c0 + 4 * u + lq, cc = min(c, rn - 1);
-                    R.ok[u] = c < rn;
-                    const __amdgpu_buffer_rsrc_t rx = buf_rsrc(a.Xt + j0, 0xFFFFFFFFu);
-                    const uint32_t xo = (uint32_t)(xrow[cc] * a.ldxt);
-#pragma unroll
-                    for (int p = 0; p < NP; ++p)
-                        R.a[p][u] = __builtin_bit_cast(flt2, buf_ld8<0>(rx, 4u * (xo + min(32 * p + 2 * lr, xc))));
-                    const __amdgpu_buffer_rsrc_t rb = buf_rsrc(nb, 0xFFFFFFFFu);
-                    R.b[0][u] = buf_ld4f<0>(rb, 4u * (uint32_t)(cc * nt2 + row_a));
-                    R.b[1][u] = buf_ld4f<0>(rb, 4u * (uint32_t)(cc * nt2 + row_b));
-                }
-            } else {
-                const int c0 = 16 * (r - RN);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int c = c0 + 4 * u + lq, cc = min(c, k - 1);
-                    R.ok[u] = c < k;
-                    const float *ar = a.yh + ((int64_t)t * k + cc) * a.ldh + j0;
-#pragma unroll
-                    for (int p = 0; p < NP; ++p) R.a[p][u] = ld2(ar + min(32 * p + 2 * lr, xc));
-                    R.b[0][u] = ld1(vb + (int64_t)cc * nt2 + row_a);
-                    R.b[1][u] = ld1(vb + (int64_t)cc * nt2 + row_b);
-                }
-            }
-        };
-        auto multiply = [&](const CatRoundLp<NP> &R, bool basis) {
-            const bool rnd = a.round_y && basis;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-#pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    flt2 v = R.ok[u] ? R.a[p][u] : flt2{0.f, 0.f};
-                    if (rnd) v = flt2{round_bf16(v.x), round_bf16(v.y)};
-#pragma unroll
-                    for (int hj = 0; hj < 2; ++hj) {
-                        if (t0)
-                            acc[2 * p + hj][0] =
-                                __builtin_amdgcn_mfma_f32_16x16x4f32(v[hj], R.b[0][u], acc[2 * p + hj][0], 0, 0, 0);
-                        if (t1)
-                            acc[2 * p + hj][1] =
-                                __builtin_amdgcn_mfma_f32_16x16x4f32(v[hj], R.b[1][u], acc[2 * p + hj][1], 0, 0, 0);
-                    }
-                }
-            }
-        };
-
-        if (g < RT) {
-            const int last = g + ((RT - 1 - g) / G) * G;  // the wave's last round
-            CatRoundLp<NP> s0, s1, s2;
-            int r = g;
-            load(r, s0);
-            load(min(r + G, last), s1);
-            // three register sets in turn; a set is loaded two rounds ahead of its use
-            for (;;) {
-                load(min(r + 2 * G, last), s2);
-                multiply(s0, r >= RN);
-                r += G;
-                if (r > last) break;
-                load(min(r + 2 * G, last), s0);
-                multiply(s1, r >= RN);
-                r += G;
-                if (r > last) break;
-                load(min(r + 2 * G, last), s1);
-                multiply(s2, r >= RN);
-                r += G;
-                if (r > last) break;
-            }
-        }
-        // partial tiles of the G waves of each row group, added in wave order.  Lane l,
-        // register q of acc[2p + hj][I] -> column 32p + 2 (4 (l / 16) + q) + hj, row
-        // 16 (tl0 + I) + l % 16.
-        for (int gg = 0; gg < G; ++gg) {
-            if (g == gg)
-#pragma unroll
-                for (int J = 0; J < 2 * NP; ++J)
-#pragma unroll
-                    for (int I = 0; I < 2; ++I)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int col = 32 * (J >> 1) + 2 * (4 * lq + q) + (J & 1);
-                            const int row = 16 * (tl0 + I) + lr;
-                            float *cell = &red[row * LDR + col];
-                            *cell = (gg == 0) ? acc[J][I][q] : *cell + acc[J][I][q];
-                        }
-            __syncthreads();
-        }
-        for (int x = threadIdx.x; x < ic * MC; x += 256) {
+        if (ic <= 32)
+            leaf_cat_lp_chunk<NC, 2, 4, NW>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+        else if (NW == 4)  // two waves per 32 rows
+            leaf_cat_lp_chunk<NC, 2, 2, 2>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0 + 32 * (w >> 1),
+                                           w < 2 ? 32 : ic - 32, j0, xc, xrow, red + (w >> 1) * 32 * LDR);
+        else if (ic <= 48)
+            leaf_cat_lp_chunk<NC, 3, 2, 2>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+        else
+            leaf_cat_lp_chunk<NC, 4, 2, 2>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+        for (int x = threadIdx.x; x < ic * MC; x += 64 * NW) {
             const int i = x / MC, j = x - i * MC;
             if (j < mc) {
                 int64_t row = r0 + i0 + i;

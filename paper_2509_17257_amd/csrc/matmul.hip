@@ -353,9 +353,10 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     const unsigned gl = (unsigned)((m + 32 * NP - 1) / (32 * NP));
     // leaf stage: one contraction per leaf (built-in where its LDS table of near rows fits),
     // a 64-row tile per wave and term, or the rows split over the waves
-    const size_t cat_lds = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
+    const size_t table = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
+    const size_t cat_lds = std::max(table, sizeof(double) * 64 * (32 * NP + 1));
     // (it reads the rows of X through a buffer resource: 32-bit byte offsets)
-    const bool cat_ok = !dm.cplx && cat_lds + sizeof(double) * 64 * (32 * NP + 1) + 64 <= 65536 &&
+    const bool cat_ok = !dm.cplx && table + sizeof(double) * 64 * (32 * NP + 1) + 64 <= 65536 &&
                         sizeof(double) * (size_t)dm.n * (size_t)ldxt < ((size_t)1 << 32);
     const int kind = cfg.leaf_kind == 0 ? (cat_ok ? 3 : 1) : (cfg.leaf_kind == 3 && !cat_ok ? 1 : cfg.leaf_kind);
     const bool rows = kind == 2;
@@ -438,7 +439,7 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     for (int d = dm.depth_max - 1; d >= P.adm_depth; --d) n_levels += P.lvl_inner_ptr[d + 1] > P.lvl_inner_ptr[d];
     for (int d = std::max(1, P.adm_depth + 1); d <= dm.depth_max; ++d) n_levels += P.lvl_ptr[d + 1] > P.lvl_ptr[d];
     const size_t lvl_lds = std::max(sizeof(double) * 2 * 64 * (16 * NJ + 1),
-                                    sizeof(double) * 64 * (32 * NP + 1) + cat_lds);
+                                    cat_lds);
     const bool inter = kind == 3 && t64 && dm.n_near > 0 && n_levels > 0 && !ov && !split && cfg.fuse_up != 1 &&
                        cfg.overlap == 5 && lvl_lds <= 65536;
     const int64_t share = n_levels > 0 ? (cat_slots + n_levels - 1) / n_levels : 0;
@@ -637,11 +638,12 @@ void matmul_gen_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alph
     kron::down_levels_p<1>(dm, m, std::max(1, P.adm_depth + 1), dm.depth_max, yh, ldh, st, sk);
     mark(4);
     const int NP = cfg.np_leaf ? cfg.np_leaf : (m > 32 ? 2 : 1);
-    const size_t cat_lds = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
+    const size_t table = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
+    const size_t cat_lds = std::max(table, sizeof(double) * 64 * (32 * NP + 1));
     const unsigned gl = (unsigned)((m + 32 * NP - 1) / (32 * NP));
     // one contraction per leaf where its table of near rows fits in LDS (and X in 32-bit byte
     // offsets), else the generic tiles
-    if (cat_lds + sizeof(double) * 64 * (32 * NP + 1) + 64 <= 65536 &&
+    if (table + sizeof(double) * 64 * (32 * NP + 1) + 64 <= 65536 &&
         sizeof(double) * (size_t)dm.n * (size_t)ldxt < ((size_t)1 << 32)) {
         const int64_t slots = (int64_t)8 * ((dm.L + 7) / 8) * gl;
         const mfma::LeafCatArgs a{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm,
@@ -789,20 +791,39 @@ hipError_t matmul_lp(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
         const int NPl = cfg.np_leaf ? cfg.np_leaf : (m > 32 ? 2 : 1);
         // one contraction per leaf (built-in where its table of near rows fits in LDS;
         // leaf_kind 3 or 0), else a 64-row tile per wave and term (leaf_kind 1 or 2)
-        const size_t cat_lds = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
-        const size_t red = NPl == 2 ? lp::leaf_cat_lp_red_bytes<2>() : lp::leaf_cat_lp_red_bytes<1>();
+        const size_t table = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
+        // the slabs of at most 32 NPl columns that cover m, narrowed to equal numbers of 16-column tiles
+        const int nslab = (int)((m + 32 * NPl - 1) / (32 * NPl)), NC = (int)(((m + 15) / 16 + nslab - 1) / nslab);
+        const size_t red = sizeof(float) * 64 * (16 * NC + 1);
         // (it reads the rows of X through a buffer resource: 32-bit byte offsets)
-        const bool cat_ok = !dm.cplx && cat_lds + red + 64 <= 65536 &&
+        const size_t cat_lds = std::max(table, red);
+        const bool cat_ok = !dm.cplx && table + sizeof(float) * 64 * (32 * NPl + 1) + 64 <= 65536 &&
                             sizeof(float) * (size_t)dm.n * (size_t)ldxt < ((size_t)1 << 32);
         if (cat_ok && (cfg.leaf_kind == 0 || cfg.leaf_kind == 3)) {
             const lp::LeafCatLpArgs a{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm,
                                       dm.Vt, dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off,
                                       (const float *)dm.N, xt, ldxt, alpha, beta, Y, ldy, to, rb, sk};
-            const unsigned grid = gl8 * (unsigned)((m + 32 * NPl - 1) / (32 * NPl));
-            if (NPl == 2)
-                hipLaunchKernelGGL((lp::k_leaf_cat_lp<2, T>), dim3(grid), dim3(256), cat_lds, st, a);
-            else
-                hipLaunchKernelGGL((lp::k_leaf_cat_lp<1, T>), dim3(grid), dim3(256), cat_lds, st, a);
+            const unsigned grid = gl8 * (unsigned)((m + 16 * NC - 1) / (16 * NC));
+            // Two waves per (leaf, slab) hold every operand once and win where they fill the chip more
+            // than twice (1024 fit at a time) and hold three or four row tiles; else four waves:
+            // n = 262144, 64 columns, FP32, 6002 leaves 8320 (two) / 8590 us (four) per product,
+            // n = 130000 3037 leaves 1436 / 1454, n = 65536 1543 leaves 770 / 765, n = 16000 362
+            // leaves 818 / 659; leaves of up to 32 rows, 4301 of them 2435 / 2346.
+            const bool two = grid >= 2048 && dm.max_leaf > 32;
+            auto go = [&](auto n) {
+                if (two)
+                    hipLaunchKernelGGL((lp::k_leaf_cat_lp<decltype(n)::value, 2, T>), dim3(grid), dim3(128), cat_lds, st,
+                                       a);
+                else
+                    hipLaunchKernelGGL((lp::k_leaf_cat_lp<decltype(n)::value, 4, T>), dim3(grid), dim3(256), cat_lds, st,
+                                       a);
+            };
+            switch (NC) {
+                case 1: go(std::integral_constant<int, 1>{}); break;
+                case 2: go(std::integral_constant<int, 2>{}); break;
+                case 3: go(std::integral_constant<int, 3>{}); break;
+                default: go(std::integral_constant<int, 4>{}); break;
+            }
         } else if (NPl == 2)
             hipLaunchKernelGGL((lp::k_leaf_lp<2, T>), dim3(gl8 * (unsigned)((m + 63) / 64)), dim3(256), 0, st,
                                dm.k, m, dm.L, dm.leaves, dm.first, dm.size, dm.perm, (const T *)dm.Vt, dm.vt_off,
