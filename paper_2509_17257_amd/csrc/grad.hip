@@ -476,7 +476,7 @@ hipError_t run_dell_fused(const DevMat &dm, const DellShape &ds, int64_t m, cons
                            lddy, w.dYt, ldh);
         const mfma::LeafCatArgs a{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm, (const double *)dm.Vt,
                                   dm.vt_off, nullptr, 0, dm.near_ptr, dm.near_col, dm.near_off, (const double *)dm.N,
-                                  w.Xt, ldh, 1.0, 0.0, nullptr, 0, 1, 0, 1, Skip{}};
+                                  w.Xt, ldh, 1.0, 0.0, nullptr, 0, 1, 0, 1, Skip{}, 0};
         const double ie = 1.0 / dm.ell;
         const mfma::DellArgs d{dm.pts, ie, ie * ie, w.dYt, ldh};
         hipLaunchKernelGGL(mfma::k_dell_near<1>, dim3((unsigned)ds.near_slots), dim3(256), ds.near_lds, st, a, d, pn);

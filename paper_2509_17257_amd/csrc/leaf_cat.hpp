@@ -12,21 +12,34 @@
 // in 16-row tiles, so a leaf of 43 points and 1100 near rows costs 48 x 1104 instead of
 // 64 x 1152 terms per column.
 //
-// Work-group: 4 waves for one (leaf, slab of 32 * NP columns).  A wave holds at most two
-// 16-row tiles: leaves of up to 32 rows are one row group and the 4 waves split the rounds
-// (wave w takes rounds w, w + 4, ...); larger leaves are two row groups of two tiles, each
-// split over 2 waves.  The partial tiles of the waves of a row group are added in LDS in
-// wave order (a fixed order: the result is reproducible).  Three register sets keep two
-// rounds of loads in flight behind the matrix-core work of the current one; every load is
-// issued unconditionally from a clamped in-range address (a round past the wave's last
-// re-reads that round, which the cache serves) so that the compiler's wait counts stay
-// exact, and rows past a segment are zeroed where they are used.
+// Work-group: four waves for one (leaf, slab of 16 NC columns).  Chunks of up to 32 rows of a leaf
+// are one row group and the waves split the rounds (wave w takes rounds w, w + 4, ...); larger
+// chunks are two row groups of two tiles, each split over two waves (64 columns and three row
+// tiles: two column halves).  With two waves per work-group each takes every second round for all
+// rows.  The partial tiles are added in LDS in wave order (a fixed order, the same for every form:
+// the result is reproducible and does not depend on the form).  Complex operators: every wave
+// all rows of every fourth round.  One or two further rounds of
+// loads stay in flight behind the matrix-core work of the current one; every load is issued
+// unconditionally from a clamped in-range address (a round past the wave's last re-reads that
+// round, which the cache serves) so that the compiler's wait counts stay exact, and rows past
+// a segment are zeroed where they are used.  A complex operator's near field is two sets of
+// rounds over the same rows, its real plane on X and its imaginary plane on J X.
+//
+// Bound by HBM for few columns and by the matrix cores from 64 on; what is lost is latency: the
+// chain of tables before a leaf's first load, and too few loads in flight.  Slabs of 16-column
+// tiles (32 or 64 columns before), pairs of rows by one 16-byte load, the row table in the LDS
+// of the partial tiles (one more work-group per CU), and the complex operator in this form:
+// product at n = 65536, m = 1 633 -> 594 us; n = 32768, leaf 128, m = 16 720 -> 671 us; complex
+// n = 32768, 8 columns 715 -> 629 us.  Three register sets at two column tiles spill.
 //
 // Lane layout of v_mfma_f64_16x16x4f64 (A: 16 x 4, B: 4 x 16, D: 16 x 16): lane l holds
 // A[l % 16][l / 16], B[l / 16][l % 16] and D rows l / 16 + 4 r, column l % 16 (r = 0..3).
-// Here A = X^T (M over columns of X: a lane loads two neighbouring columns with one 16-byte
-// load, which feed an "even" and an "odd" column tile), B = N^T (N over rows of the leaf).
+// Here A = X^T (M over columns of X), B = N^T (N over rows of the leaf): a lane loads two
+// neighbouring columns (rows) with one 16-byte load, which feed an "even" and an "odd" tile; an
+// odd last tile is loaded by 8 bytes per lane.
 #pragma once
+
+#include <type_traits>
 
 #include "device.hpp"
 #include "stages_mfma.hpp"
@@ -37,18 +50,13 @@ namespace mfma {
 typedef double dbl4c __attribute__((ext_vector_type(4)));
 typedef double dbl2c __attribute__((ext_vector_type(2)));
 
-template <int NP>
+// registers of one round of a wave (NC column tiles, NT row tiles)
+template <int NC, int NT>
 struct CatRound {
-    dbl2c a[NP][4];  // [column half p][k-step u]: columns 32p + 2 (l % 16) + {0, 1}
-    double b[2][4];  // [row tile of the wave][k-step u]: row 16 I + l % 16
-    int ok[4];       // k-row of step u inside its segment
-};
-
-// registers of one round of a wave that takes one 32-column half and three row tiles
-struct CatHalf {
-    dbl2c a[4];      // [k-step u]: columns 32 (w >> 1) + 2 (l % 16) + {0, 1}
-    double b[3][4];  // [row tile][k-step u]
-    int ok[4];
+    dbl2c a[NC / 2 + 1][4];  // [column pair p][k-step u]: columns 32p + 2 (l % 16) + {0, 1}
+    double c[4];             // [k-step u], NC odd: column 16 (NC - 1) + l % 16
+    dbl2c b[NT / 2][4];      // [row pair q][k-step u]: rows 32q + 2 (l % 16) + {0, 1}
+    double d[4];             // [k-step u], NT odd: row 16 (NT - 1) + l % 16
 };
 
 // rows of the near field of one leaf, as a table of tree positions in LDS (built from the
@@ -92,33 +100,166 @@ struct LeafCatArgs {
     int64_t ldy;
     int tree_order, basis, near;
     Skip skip;
+    int64_t n_plane;  // complex operator: offset of the imaginary parts in Nt, else 0
 };
 
-// LDS of the leaf work: the partial-tile buffer, then the near-row table
-template <int NP>
-constexpr size_t leaf_cat_red_bytes() { return sizeof(double) * 64 * (32 * NP + 1); }
+// LDS of the leaf work: the near-row table, then the partial tiles of a slab of 16 NC columns
+__host__ __device__ constexpr size_t leaf_cat_red_bytes(int NC) { return sizeof(double) * 64 * (16 * NC + 1); }
 
-// one (leaf, column slab) slot: slot & 7 is the XCD, whose leaves form one contiguous
-// eighth (taken in the order of a.order: the most work first); the slabs of one leaf are
-// consecutive slots of one XCD, so its near blocks come from HBM once.  red: 64 x (32 NP + 1) doubles of LDS; xrow: the near-row table.
-template <int NP>
-__device__ inline void leaf_cat_slot(int64_t slot, const LeafCatArgs &a, double *red) {
+// NT row tiles from row i0 on (ic of these rows present) and NC column tiles from column j0 on.  The
+// rounds are summed in G groups (group r % G: two where the chunk has three or four row tiles, four
+// below); of the GW waves of these rows, wave g takes the groups g, g + GW, .. in turn.  The
+// groups' partial tiles are added in LDS in order (red: the first cell, rows of LDR).  CPX: the
+// near rounds run on two waves for the real plane on X and on two for the imaginary plane on J X
+// (column pairs (re, im) -> (-im, re)), so the large diagonal entries meet a quarter of the terms.
+template <int NC, int NT, int G, int GW, int LDR, bool CPX>
+__device__ inline void leaf_cat_chunk(const LeafCatArgs &a, int g, int lr, int lq, int32_t t, const double *nb,
+                                      const double *vb, int32_t rn, int64_t nt2, int i0, int ic, int64_t j0, int xc,
+                                      const int32_t *xrow, double *red) {
+    constexpr int NA = G / GW, NPR = NC / 2;
+    const int k = a.k;
+    const int RN = (rn + 15) >> 4, RI = CPX ? 4 * ((RN + 1) >> 1) : RN, RT = RI + (a.basis ? (k + 15) >> 4 : 0);
+    // (row lengths are even: a pair stays inside its row; the blocks of a leaf are below 4 GiB, as
+    // their table fits in LDS)
+    const uint32_t len = (uint32_t)nt2;
+    uint32_t row[NT / 2];
+#pragma unroll
+    for (int q = 0; q < NT / 2; ++q) row[q] = (uint32_t)(i0 + min(32 * q + 2 * lr, (ic - 1) & ~1));
+    const uint32_t rs = (uint32_t)(i0 + min(16 * (NT - 1) + lr, ic - 1));
+    uint32_t cp[NPR + 1];
+#pragma unroll
+    for (int p = 0; p < NPR; ++p) cp[p] = (uint32_t)min(32 * p + 2 * lr, xc);
+    const uint32_t cs = (uint32_t)min(16 * (NC - 1) + lr, xc + 1);
+
+    dbl4c acc[NA][NC][NT];
+#pragma unroll
+    for (int x = 0; x < NA; ++x)
+#pragma unroll
+        for (int J = 0; J < NC; ++J)
+#pragma unroll
+            for (int I = 0; I < NT; ++I) acc[x][J][I] = dbl4c{0.0, 0.0, 0.0, 0.0};
+
+    // rows 16 near_round(r).. of the near field: of four rounds of a complex operator the first two
+    // are the real plane's, the last two the imaginary plane's
+    auto near_round = [](int r) { return CPX ? 2 * (r >> 2) + (r & 1) : r; };
+    // round r -> registers, from clamped in-range addresses (X and y_t: 32-bit byte offsets)
+    auto load = [&](int r, CatRound<NC, NT> &R) {
+        const bool nr = r < RI, im = CPX && nr && (r & 2);
+        const double *ab = nr ? a.Xt + j0 : a.yh + (int64_t)t * k * a.ldh + j0;
+        const int64_t lda = nr ? a.ldxt : a.ldh;
+        const double *bb = nr ? nb + (im ? a.n_plane : 0) : vb;
+        const int c0 = 16 * (nr ? near_round(r) : r - RI), lim = nr ? rn : k;
+        const uint32_t sw = im ? 1 : 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int cc = min(c0 + 4 * u + lq, lim - 1);
+            const uint32_t ao = (uint32_t)((nr ? (int64_t)xrow[cc] : (int64_t)cc) * lda);
+#pragma unroll
+            for (int p = 0; p < NPR; ++p)
+                R.a[p][u] = __builtin_bit_cast(dbl2c, buf_ld16<0>(buf_rsrc(ab, 0xFFFFFFFFu), 8u * (ao + cp[p])));
+            if (NC & 1)
+                R.c[u] = __builtin_bit_cast(double, buf_ld8<0>(buf_rsrc(ab, 0xFFFFFFFFu), 8u * (ao + (cs ^ sw))));
+#pragma unroll
+            for (int q = 0; q < NT / 2; ++q)
+                R.b[q][u] = __builtin_bit_cast(dbl2c, buf_ld16<0>(buf_rsrc(bb, 0xFFFFFFFFu), 8u * (cc * len + row[q])));
+            if (NT & 1)
+                R.d[u] = __builtin_bit_cast(double, buf_ld8<0>(buf_rsrc(bb, 0xFFFFFFFFu), 8u * (cc * len + rs)));
+        }
+    };
+    // the products of round r; rows past its segment are zeroed here
+    auto multiply = [&](int r, const CatRound<NC, NT> &R, dbl4c(&ac)[NC][NT]) {
+        const bool im = CPX && r < RI && (r & 2);
+        const int rem = r < RI ? rn - 16 * near_round(r) : k - 16 * (r - RI);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool ok = 4 * u + lq < rem;
+#pragma unroll
+            for (int J = 0; J < NC; ++J) {
+                double v;
+                if ((NC & 1) && J == NC - 1) {
+                    v = R.c[u];
+                    if (im && !(lr & 1)) v = -v;
+                } else {
+                    v = R.a[J >> 1][u][J & 1];
+                    if (im) v = (J & 1) ? R.a[J >> 1][u][0] : -R.a[J >> 1][u][1];
+                }
+                v = ok ? v : 0.0;
+#pragma unroll
+                for (int I = 0; I < NT; ++I)
+                    ac[J][I] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                        v, ((NT & 1) && I == NT - 1) ? R.d[u] : R.b[I >> 1][u][I & 1], ac[J][I], 0, 0, 0);
+            }
+        }
+    };
+
+    if (g < RT) {
+        const int last = g + ((RT - 1 - g) / GW) * GW;  // the wave's last round
+        int r = g;
+        if constexpr (NA == 1 && NC * NT <= 2) {
+            // three register sets in turn; a set is loaded two rounds ahead of its use (a round past
+            // the last re-reads that one, which the cache serves)
+            CatRound<NC, NT> s0, s1, s2;
+            load(r, s0);
+            load(min(r + GW, last), s1);
+            for (;;) {
+                load(min(r + 2 * GW, last), s2);
+                multiply(r, s0, acc[0]);
+                if ((r += GW) > last) break;
+                load(min(r + 2 * GW, last), s0);
+                multiply(r, s1, acc[0]);
+                if ((r += GW) > last) break;
+                load(min(r + 2 * GW, last), s1);
+                multiply(r, s2, acc[0]);
+                if ((r += GW) > last) break;
+            }
+        } else {  // two sets, one round ahead
+            CatRound<NC, NT> s0, s1;
+            load(r, s0);
+            for (;;) {
+                load(min(r + GW, last), s1);
+                multiply(r, s0, acc[0]);
+                if ((r += GW) > last) break;
+                load(min(r + GW, last), s0);
+                multiply(r, s1, acc[NA - 1]);
+                if ((r += GW) > last) break;
+            }
+        }
+    }
+    __syncthreads();  // the row table was read for the last time: its LDS takes the partial tiles
+    // Lane l, register q of a pair tile J -> column 32 (J / 2) + 2 (l / 16 + 4 q) + J % 2, of a single
+    // last tile -> column 16 (NC - 1) + l / 16 + 4 q; rows as in the loads.
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+        if (g == gg % GW)
+#pragma unroll
+            for (int J = 0; J < NC; ++J)
+#pragma unroll
+                for (int I = 0; I < NT; ++I) {
+                    const int rw = ((NT & 1) && I == NT - 1) ? 16 * I + lr : 32 * (I >> 1) + 2 * lr + (I & 1);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int col = ((NC & 1) && J == NC - 1) ? 16 * J + lq + 4 * q
+                                                                  : 32 * (J >> 1) + 2 * (lq + 4 * q) + (J & 1);
+                        double *cell = &red[rw * LDR + col];
+                        const double v = acc[gg / GW][J][I][q];
+                        *cell = (gg == 0) ? v : *cell + v;
+                    }
+                }
+        __syncthreads();
+    }
+}
+
+// columns j0..j0 + 16 NC - 1 of leaf l by NW waves; red: the dynamic LDS
+template <int NC, int NW, bool CPX>
+__device__ inline void leaf_cat_slab(int32_t l, int64_t j0, const LeafCatArgs &a, double *red) {
+    constexpr int MC = 16 * NC, LDR = MC + 1;
     int32_t *xrow = (int32_t *)red;
-    constexpr int MC = 32 * NP, LDR = MC + 1;
-    const int32_t per_xcd = (a.L + 7) / 8;
-    const int nslab = (int)((a.m + MC - 1) / MC);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, lr = lane & 15,
               lq = lane >> 4;
-    const int64_t qx = slot >> 3;
-    const int32_t pos = (int32_t)((slot & 7) * per_xcd + qx / nslab);
-    if (pos >= a.L) return;
-    const int32_t l = a.order[pos];
     const int32_t t = a.leaves[l];
     if (a.skip(t)) return;
-    const int k = a.k;
     const int nt = a.size[t];
     const int64_t nt2 = pad_rows(nt), r0 = a.first[t];
-    const int64_t j0 = (qx % nslab) * MC;
     const int mc = (int)min<int64_t>(MC, a.m - j0);
     const int64_t q0 = a.near_ptr[l];
     const int nnear = a.near ? (int)(a.near_ptr[l + 1] - q0) : 0;
@@ -129,191 +270,29 @@ __device__ inline void leaf_cat_slot(int64_t slot, const LeafCatArgs &a, double 
     for (int i0 = 0; i0 < nt; i0 += 64) {
         const int32_t rn =
             nnear > 0 ? cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size) : 0;
-        const int RN = (rn + 15) >> 4, RB = a.basis ? (k + 15) >> 4 : 0, RT = RN + RB;
         const int ic = min(64, nt - i0);
-        const int ntile = (ic + 15) >> 4;
-        if (NP == 2 && ntile == 3) {
-            // 64 columns, 33-48 rows: wave w takes the column half w >> 1 and the k-group w & 1
-            // for all three row tiles, so every wave has the same matrix-core work and each X
-            // row is loaded once (two row groups would give one wave pair a single tile and
-            // load the X rows twice); the same rounds per k-group and the same order of adds
-            // as the row groups, so the result is the same bit for bit
-            const int ch = w >> 1, g = w & 1;
-            int rw[3];
-#pragma unroll
-            for (int I = 0; I < 3; ++I) rw[I] = i0 + min(16 * I + lr, ic - 1);
-            dbl4c acc[2][3];
-#pragma unroll
-            for (int hj = 0; hj < 2; ++hj)
-#pragma unroll
-                for (int I = 0; I < 3; ++I) acc[hj][I] = dbl4c{0.0, 0.0, 0.0, 0.0};
-            auto load = [&](int r, CatHalf &R) {
-                const bool nr = r < RN;
-                const double *ab = nr ? a.Xt + j0 : a.yh + (int64_t)t * k * a.ldh + j0;
-                const int64_t lda = nr ? a.ldxt : a.ldh;
-                const double *bb = nr ? nb : vb;
-                const int c0 = nr ? 16 * r : 16 * (r - RN), lim = nr ? rn : k;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int c = c0 + 4 * u + lq, cc = min(c, lim - 1);
-                    R.ok[u] = c < lim;
-                    const int64_t arow = nr ? (int64_t)xrow[cc] : (int64_t)cc;
-                    R.a[u] = __builtin_bit_cast(
-                        dbl2c, buf_ld16<0>(buf_rsrc(ab, 0xFFFFFFFFu),
-                                           8u * (uint32_t)(arow * lda + min(32 * ch + 2 * lr, xc))));
-#pragma unroll
-                    for (int I = 0; I < 3; ++I) R.b[I][u] = bb[(int64_t)cc * nt2 + rw[I]];
-                }
-            };
-            auto multiply = [&](CatHalf &R) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const dbl2c v = R.ok[u] ? R.a[u] : dbl2c{0.0, 0.0};
-#pragma unroll
-                    for (int hj = 0; hj < 2; ++hj)
-#pragma unroll
-                        for (int I = 0; I < 3; ++I)
-                            acc[hj][I] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[hj], R.b[I][u], acc[hj][I], 0, 0, 0);
-                }
-            };
-            if (g < RT) {
-                const int last = g + ((RT - 1 - g) / 2) * 2;
-                CatHalf s0, s1;  // two register sets in turn: one round of loads in flight
-                int r = g;
-                load(r, s0);
-                for (;;) {
-                    load(min(r + 2, last), s1);
-                    multiply(s0);
-                    r += 2;
-                    if (r > last) break;
-                    load(min(r + 2, last), s0);
-                    multiply(s1);
-                    r += 2;
-                    if (r > last) break;
-                }
-            }
-            __syncthreads();  // the row table is read for the last time: its LDS takes the partial tiles
-            for (int gg = 0; gg < 2; ++gg) {
-                if (g == gg)
-#pragma unroll
-                    for (int hj = 0; hj < 2; ++hj)
-#pragma unroll
-                        for (int I = 0; I < 3; ++I)
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const int col = 32 * ch + 2 * (lq + 4 * q) + hj;
-                                double *cell = &red[(16 * I + lr) * LDR + col];
-                                *cell = (gg == 0) ? acc[hj][I][q] : *cell + acc[hj][I][q];
-                            }
-                __syncthreads();
-            }
-        } else {
-            const int G = ntile > 2 ? 2 : 4;          // waves per row group (k-groups)
-            const int wr = w / G, g = w - wr * G;     // row group, k-group (wave-uniform)
-            const int tl0 = 2 * wr;                   // first row tile of the wave
-            const bool t0 = tl0 < ntile, t1 = tl0 + 1 < ntile;
-            const int row_a = i0 + min(16 * tl0 + lr, ic - 1), row_b = i0 + min(16 * tl0 + 16 + lr, ic - 1);
-
-            dbl4c acc[2 * NP][2];
-    #pragma unroll
-            for (int J = 0; J < 2 * NP; ++J) acc[J][0] = acc[J][1] = dbl4c{0.0, 0.0, 0.0, 0.0};
-
-            // round r (clamped to the wave's rounds) -> registers
-            auto load = [&](int r, CatRound<NP> &R) {
-                const bool nr = r < RN;
-                const double *ab;
-                int64_t lda;
-                const double *bb;
-                int c0, lim;
-                if (nr) {
-                    c0 = 16 * r;
-                    lim = rn;
-                    bb = nb;
-                    lda = a.ldxt;
-                    ab = a.Xt + j0;
-                } else {
-                    c0 = 16 * (r - RN);
-                    lim = k;
-                    bb = vb;
-                    lda = a.ldh;
-                    ab = a.yh + (int64_t)t * k * a.ldh + j0;
-                }
-    #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int c = c0 + 4 * u + lq, cc = min(c, lim - 1);
-                    R.ok[u] = c < lim;
-                    const int64_t arow = nr ? (int64_t)xrow[cc] : (int64_t)cc;
-    #pragma unroll
-                    for (int p = 0; p < NP; ++p)
-                        R.a[p][u] = __builtin_bit_cast(
-                            dbl2c, buf_ld16<0>(buf_rsrc(ab, 0xFFFFFFFFu),
-                                               8u * (uint32_t)(arow * lda + min(32 * p + 2 * lr, xc))));
-                    R.b[0][u] = bb[(int64_t)cc * nt2 + row_a];
-                    R.b[1][u] = bb[(int64_t)cc * nt2 + row_b];
-                }
-            };
-            auto multiply = [&](CatRound<NP> &R) {
-    #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-    #pragma unroll
-                    for (int p = 0; p < NP; ++p) {
-                        const dbl2c v = R.ok[u] ? R.a[p][u] : dbl2c{0.0, 0.0};
-    #pragma unroll
-                        for (int hj = 0; hj < 2; ++hj) {
-                            if (t0)
-                                acc[2 * p + hj][0] =
-                                    __builtin_amdgcn_mfma_f64_16x16x4f64(v[hj], R.b[0][u], acc[2 * p + hj][0], 0, 0, 0);
-                            if (t1)
-                                acc[2 * p + hj][1] =
-                                    __builtin_amdgcn_mfma_f64_16x16x4f64(v[hj], R.b[1][u], acc[2 * p + hj][1], 0, 0, 0);
-                        }
-                    }
-                }
-            };
-
-            if (g < RT) {
-                const int last = g + ((RT - 1 - g) / G) * G;  // the wave's last round
-                CatRound<NP> s0, s1, s2;
-                int r = g;
-                load(r, s0);
-                load(min(r + G, last), s1);
-                // three register sets in turn; a set is loaded two rounds ahead of its use
-                for (;;) {
-                    load(min(r + 2 * G, last), s2);
-                    multiply(s0);
-                    r += G;
-                    if (r > last) break;
-                    load(min(r + 2 * G, last), s0);
-                    multiply(s1);
-                    r += G;
-                    if (r > last) break;
-                    load(min(r + 2 * G, last), s1);
-                    multiply(s2);
-                    r += G;
-                    if (r > last) break;
-                }
-            }
-            __syncthreads();  // the row table is read for the last time: its LDS takes the partial tiles
-            // partial tiles of the G waves of each row group, added in wave order.  Lane l,
-            // register q of acc[2p + hj][I] -> column 32p + 2 (l / 16 + 4 q) + hj, row
-            // 16 (tl0 + I) + l % 16.
-            for (int gg = 0; gg < G; ++gg) {
-                if (g == gg)
-    #pragma unroll
-                    for (int J = 0; J < 2 * NP; ++J)
-    #pragma unroll
-                        for (int I = 0; I < 2; ++I)
-    #pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const int col = 32 * (J >> 1) + 2 * (lq + 4 * q) + (J & 1);
-                                const int row = 16 * (tl0 + I) + lr;
-                                double *cell = &red[row * LDR + col];
-                                *cell = (gg == 0) ? acc[J][I][q] : *cell + acc[J][I][q];
-                            }
-                __syncthreads();
-            }
+        if constexpr (CPX) {  // four groups: the sums are twice as long
+            if (ic <= 32)
+                leaf_cat_chunk<NC, 2, 4, 4, LDR, true>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+            else if (ic <= 48)
+                leaf_cat_chunk<NC, 3, 4, 4, LDR, true>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+            else
+                leaf_cat_chunk<NC, 4, 4, 4, LDR, true>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+        } else if (ic <= 32)
+            leaf_cat_chunk<NC, 2, 4, NW, LDR, CPX>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+        else if (NW == 4 && NC == 4 && ic <= 48)  // two waves per 32 columns: equal work for three row tiles
+            leaf_cat_chunk<2, 3, 2, 2, LDR, CPX>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0 + 32 * (w >> 1),
+                                                 max(xc - 32 * (w >> 1), 0), xrow, red + 32 * (w >> 1));
+        else if (NW == 4)  // two waves per 32 rows
+            leaf_cat_chunk<NC, 2, 2, 2, LDR, CPX>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0 + 32 * (w >> 1),
+                                                  w < 2 ? 32 : ic - 32, j0, xc, xrow, red + (w >> 1) * 32 * LDR);
+        else if constexpr (NW == 2) {
+            if (ic <= 48)
+                leaf_cat_chunk<NC, 3, 2, 2, LDR, CPX>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+            else
+                leaf_cat_chunk<NC, 4, 2, 2, LDR, CPX>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
         }
-        for (int x = threadIdx.x; x < ic * MC; x += 256) {
+        for (int x = threadIdx.x; x < ic * MC; x += 64 * NW) {
             const int i = x / MC, j = x - i * MC;
             if (j < mc) {
                 int64_t row = r0 + i0 + i;
@@ -325,6 +304,26 @@ __device__ inline void leaf_cat_slot(int64_t slot, const LeafCatArgs &a, double 
         }
         __syncthreads();
     }
+}
+
+// one (leaf, column slab) slot: slot & 7 is the XCD, whose leaves form one contiguous
+// eighth (taken in the order of a.order: the most work first); the slabs of one leaf are
+// consecutive slots of one XCD, so its near blocks come from HBM once.
+template <int NC, int NW, bool CPX>
+__device__ inline void leaf_cat_slot(int64_t slot, const LeafCatArgs &a, double *red) {
+    const int32_t per_xcd = (a.L + 7) / 8;
+    const int nslab = (int)((a.m + 16 * NC - 1) / (16 * NC));
+    const int64_t qx = slot >> 3;
+    const int32_t pos = (int32_t)((slot & 7) * per_xcd + qx / nslab);
+    if (pos >= a.L) return;
+    const int32_t l = a.order[pos];
+    const int64_t j0 = (qx % nslab) * (16 * NC);
+    if (NC == 4 && a.m - j0 <= 32)
+        leaf_cat_slab<2, NW, CPX>(l, j0, a, red);
+    else if (NC == 4 && a.m - j0 <= 48)
+        leaf_cat_slab<3, NW, CPX>(l, j0, a, red);
+    else
+        leaf_cat_slab<NC, NW, CPX>(l, j0, a, red);
 }
 
 // ---- the near-field term of d ell ----
@@ -495,11 +494,25 @@ __global__ __launch_bounds__(256, 2) void k_dell_near(LeafCatArgs a, DellArgs d,
     if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
-// the leaf stage over slots [slot0, slot1): dynamic LDS = the near-row table
-template <int NP>
-__global__ __launch_bounds__(256, NP == 1 ? 3 : 2) void k_leaf_cat(LeafCatArgs a, int64_t slot0, int64_t slot1) {
+// the leaf stage over slots [slot0, slot1): dynamic LDS = the near-row table and the partial tiles
+template <int NC, int NW, bool CPX>
+__global__ __launch_bounds__(64 * NW, (NC == 1 || (NW == 4 && NC == 2)) && !CPX ? 3 : 2) void k_leaf_cat(LeafCatArgs a, int64_t slot0, int64_t slot1) {
     extern __shared__ double red[];
-    for (int64_t slot = slot0 + blockIdx.x; slot < slot1; slot += gridDim.x) leaf_cat_slot<NP>(slot, a, red);
+    for (int64_t slot = slot0 + blockIdx.x; slot < slot1; slot += gridDim.x) leaf_cat_slot<NC, NW, CPX>(slot, a, red);
+}
+
+// calls f(k_leaf_cat<..>) for the column tiles, waves and kind of operator of one launch
+// (two waves: nc = 2, real operators; complex operators: nc <= 2)
+template <typename F>
+void leaf_cat_kernel(int nc, bool two, bool cplx, F f) {
+    if (cplx) return nc == 1 ? f(&k_leaf_cat<1, 4, true>, 256) : f(&k_leaf_cat<2, 4, true>, 256);
+    if (two) return f(&k_leaf_cat<2, 2, false>, 128);
+    switch (nc) {
+        case 1: return f(&k_leaf_cat<1, 4, false>, 256);
+        case 2: return f(&k_leaf_cat<2, 4, false>, 256);
+        case 3: return f(&k_leaf_cat<3, 4, false>, 256);
+        default: return f(&k_leaf_cat<4, 4, false>, 256);
+    }
 }
 
 // A transfer level with a share of the near field beside it: work-groups [0, items) run the
@@ -523,7 +536,7 @@ __global__ __launch_bounds__(256, 2) void k_level_near(int64_t items, int gy, in
         else
             down64_item<NJ>(i, by, m, list, aux, E, hat, ldh, skip, lds);
     } else if (b >= items + lead) {
-        leaf_cat_slot<NP>(slot0 + (b - items - lead), a, lds);
+        leaf_cat_slot<2 * NP, 4, false>(slot0 + (b - items - lead), a, lds);
     }
 }
 

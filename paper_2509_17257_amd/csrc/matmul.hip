@@ -315,6 +315,19 @@ __global__ __launch_bounds__(256) void k_leaf_near(int k, int64_t m, const int32
 
 inline int64_t even_ld(int64_t m) { return m + (m & 1); }
 
+// leaf stage: 16-column tiles of a slab of at most 32 NP columns, narrow for few columns
+inline int cat_tiles(int64_t m, int NP) { return (int)std::min<int64_t>(2 * NP, (m + 15) / 16); }
+
+// Two waves per (leaf, slab) load every operand once; four have two row groups with the rows of X
+// loaded twice, but half the serial rounds.  Two win for 17 to 32 columns where the leaves fill the
+// chip (1024 such groups fit at a time) and have three or four row tiles: n = 65536, m = 32 780 (two) /
+// 787 us (four) per product, 16 merged systems 1535 / 1590 us.  At one tile of columns the loads
+// of X are few: m = 1 610 / 605 us; few leaves want the waves: n = 32768, leaf 128, m = 16
+// 706 / 671 us; above 32 columns the sums of two waves do not fit their registers.
+inline bool cat_two_waves(const DevMat &dm, int nc, int64_t slots) {
+    return nc == 2 && slots >= 1024 && dm.max_leaf > 32;
+}
+
 // All five stages on the matrix cores (FP64 operator, k = 64 or k <= 32).
 template <int NJ>
 void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alpha, const double *X, int64_t ldx,
@@ -354,27 +367,28 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     // leaf stage: one contraction per leaf (built-in where its LDS table of near rows fits),
     // a 64-row tile per wave and term, or the rows split over the waves
     const size_t table = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
-    const size_t cat_lds = std::max(table, sizeof(double) * 64 * (32 * NP + 1));
+    const int cat_np = dm.cplx ? 1 : NP;  // complex operators: slabs of at most 32 real columns
+    const size_t red = mfma::leaf_cat_red_bytes(2 * cat_np), cat_lds = std::max(table, red);
     // (it reads the rows of X through a buffer resource: 32-bit byte offsets)
-    const bool cat_ok = !dm.cplx && table + sizeof(double) * 64 * (32 * NP + 1) + 64 <= 65536 &&
+    const bool cat_ok = table + red + 64 <= 65536 &&
                         sizeof(double) * (size_t)dm.n * (size_t)ldxt < ((size_t)1 << 32);
     const int kind = cfg.leaf_kind == 0 ? (cat_ok ? 3 : 1) : (cfg.leaf_kind == 3 && !cat_ok ? 1 : cfg.leaf_kind);
     const bool rows = kind == 2;
-    const int64_t cat_slots = (int64_t)8 * ((dm.L + 7) / 8) * gl;
+    const int cat_nc = cat_tiles(m, cat_np);
+    const int64_t cat_slots = (int64_t)8 * ((dm.L + 7) / 8) * ((m + 16 * cat_nc - 1) / (16 * cat_nc));
+    const bool cat_two = cat_two_waves(dm, cat_nc, cat_slots);
     auto cat_args = [&](double b, int basis, int near) {
         return mfma::LeafCatArgs{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm, (const double *)dm.Vt,
                                  dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off, (const double *)dm.N, Xt,
-                                 ldxt, alpha, b, Y, ldy, to, basis, near, sk};
+                                 ldxt, alpha, b, Y, ldy, to, basis, near, sk, dm.n_plane};
     };
     auto leaf = [&](hipStream_t s, double b, int basis, int near, unsigned cap) {
         if (kind == 3) {
             const unsigned gx = (unsigned)(cap ? std::min<int64_t>(cat_slots, cap) : cat_slots);
-            if (NP == 2)
-                hipLaunchKernelGGL(mfma::k_leaf_cat<2>, dim3(gx), dim3(256), cat_lds, s, cat_args(b, basis, near),
-                                   (int64_t)0, cat_slots);
-            else
-                hipLaunchKernelGGL(mfma::k_leaf_cat<1>, dim3(gx), dim3(256), cat_lds, s, cat_args(b, basis, near),
-                                   (int64_t)0, cat_slots);
+            mfma::leaf_cat_kernel(cat_nc, cat_two, dm.cplx, [&](auto kern, int threads) {
+                hipLaunchKernelGGL(kern, dim3(gx), dim3(threads), cat_lds, s, cat_args(b, basis, near), (int64_t)0,
+                                   cat_slots);
+            });
             return;
         }
         if (rows) {
@@ -423,7 +437,7 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     // work-groups take enough LDS that a CU holds at most three of them and keeps room for a
     // transfer work-group.  The basis term follows the downward pass (not with per-stage
     // timing or the fused upward pass).
-    const bool halves = kind == 3 && t64 && dm.side && dm.n_near > 0 && cfg.overlap == 6 && !ev &&
+    const bool halves = kind == 3 && !dm.cplx && t64 && dm.side && dm.n_near > 0 && cfg.overlap == 6 && !ev &&
                         cfg.fuse_up != 1 && dm.leaf_half > 0;
     // coupling of the deep rows on the second stream beside the upper transfer levels, the
     // coupling of the other rows and the upper downward levels (not with per-stage timing,
@@ -440,7 +454,7 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     for (int d = std::max(1, P.adm_depth + 1); d <= dm.depth_max; ++d) n_levels += P.lvl_ptr[d + 1] > P.lvl_ptr[d];
     const size_t lvl_lds = std::max(sizeof(double) * 2 * 64 * (16 * NJ + 1),
                                     cat_lds);
-    const bool inter = kind == 3 && t64 && dm.n_near > 0 && n_levels > 0 && !ov && !split && cfg.fuse_up != 1 &&
+    const bool inter = kind == 3 && !dm.cplx && t64 && dm.n_near > 0 && n_levels > 0 && !ov && !split && cfg.fuse_up != 1 &&
                        cfg.overlap == 5 && lvl_lds <= 65536;
     const int64_t share = n_levels > 0 ? (cat_slots + n_levels - 1) / n_levels : 0;
     int64_t next_slot = 0;
@@ -494,7 +508,8 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
         {
             hipFuncAttributes fa{}, fu{};
             int dev = 0, per_cu = 0;
-            const void *fl = NP == 2 ? (const void *)mfma::k_leaf_cat<2> : (const void *)mfma::k_leaf_cat<1>;
+            const void *fl = nullptr;
+            mfma::leaf_cat_kernel(cat_nc, cat_two, dm.cplx, [&](auto kern, int) { fl = (const void *)kern; });
             if (hipFuncGetAttributes(&fa, fl) == hipSuccess &&
                 hipFuncGetAttributes(&fu, (const void *)kron::k_up<4, 16 * NJ>) == hipSuccess &&
                 hipGetDevice(&dev) == hipSuccess &&
@@ -507,12 +522,10 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
         }
         auto near_part = [&](int64_t s0, int64_t s1) {
             if (s1 <= s0) return;
-            if (NP == 2)
-                hipLaunchKernelGGL(mfma::k_leaf_cat<2>, dim3((unsigned)(s1 - s0)), dim3(256), dyn, dm.side,
-                                   cat_args(beta, 0, 1), s0, s1);
-            else
-                hipLaunchKernelGGL(mfma::k_leaf_cat<1>, dim3((unsigned)(s1 - s0)), dim3(256), dyn, dm.side,
-                                   cat_args(beta, 0, 1), s0, s1);
+            mfma::leaf_cat_kernel(cat_nc, cat_two, dm.cplx, [&](auto kern, int threads) {
+                hipLaunchKernelGGL(kern, dim3((unsigned)(s1 - s0)), dim3(threads), dyn, dm.side, cat_args(beta, 0, 1), s0,
+                                   s1);
+            });
         };
         // slots below sA: the first leaf_half positions of every eighth (a multiple of 8, so
         // slot s still runs on XCD s % 8)
@@ -639,20 +652,20 @@ void matmul_gen_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alph
     mark(4);
     const int NP = cfg.np_leaf ? cfg.np_leaf : (m > 32 ? 2 : 1);
     const size_t table = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
-    const size_t cat_lds = std::max(table, sizeof(double) * 64 * (32 * NP + 1));
+    const size_t red = mfma::leaf_cat_red_bytes(2 * NP), cat_lds = std::max(table, red);
     const unsigned gl = (unsigned)((m + 32 * NP - 1) / (32 * NP));
     // one contraction per leaf where its table of near rows fits in LDS (and X in 32-bit byte
     // offsets), else the generic tiles
-    if (table + sizeof(double) * 64 * (32 * NP + 1) + 64 <= 65536 &&
+    if (table + red + 64 <= 65536 &&
         sizeof(double) * (size_t)dm.n * (size_t)ldxt < ((size_t)1 << 32)) {
         const int64_t slots = (int64_t)8 * ((dm.L + 7) / 8) * gl;
         const mfma::LeafCatArgs a{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm,
                                   (const double *)dm.Vt, dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off,
-                                  (const double *)dm.N, Xt, ldxt, alpha, beta, Y, ldy, to, 1, 1, sk};
-        if (NP == 2)
-            hipLaunchKernelGGL(mfma::k_leaf_cat<2>, dim3((unsigned)slots), dim3(256), cat_lds, st, a, (int64_t)0, slots);
-        else
-            hipLaunchKernelGGL(mfma::k_leaf_cat<1>, dim3((unsigned)slots), dim3(256), cat_lds, st, a, (int64_t)0, slots);
+                                  (const double *)dm.N, Xt, ldxt, alpha, beta, Y, ldy, to, 1, 1, sk, 0};
+        const int nc = cat_tiles(m, NP);
+        mfma::leaf_cat_kernel(nc, cat_two_waves(dm, nc, slots), false, [&](auto kern, int threads) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)slots), dim3(threads), cat_lds, st, a, (int64_t)0, slots);
+        });
     } else {
         hipLaunchKernelGGL((k_leaf_near<double, double, double>), dim3(dm.L, (unsigned)((m + TC - 1) / TC)), dim3(256), 0,
                            st, dm.k, m, dm.leaves, dm.first, dm.size, dm.perm, (const double *)dm.V, yh, ldh,

@@ -61,3 +61,44 @@ def test_lowp_many_leaves(leaf, prec):
         A.set_tune(m)
         Y = h2x.h2_matmul(A, Xm)
         assert _rel(Y.cpu().numpy(), ref.cpu().numpy()) <= 1e-5, m
+
+
+@pytest.mark.parametrize("leaf,p", LEAVES)
+@pytest.mark.parametrize("cplx", [False, True], ids=["real", "complex"])
+def test_fp64_leaf(leaf, p, cplx):
+    """Against the oracle at FP64 rounding, and column by column the same bits whatever the slab."""
+    import paper_2509_17257_amd as h2x
+    n, top = 2600, 100 if not cplx else 50
+    P = W.cube_points(n, 720 + leaf)
+    prm = dict(ell=0.8, shift=1.0, eta=1.0, leaf=leaf, p=p)
+    if cplx:
+        prm["kernel"] = "helmholtz"
+    A, o = h2x.H2Matrix(P, **prm), oracle.OracleH2(P, **prm)
+    X = W.rhs(n, top, 721)
+    if cplx:
+        X = X + 1j * W.rhs(n, top, 722)
+    ref = o.matmul_complex(X) if cplx else o.matmul(X)
+    Xd = torch.from_numpy(X).cuda()
+    Y = h2x.h2_matmul(A, Xd)
+    assert _rel(Y.cpu().numpy(), ref) <= 1e-12
+    for m in ((1, 7, 8, 9, 16, 17, 24, 25, 32, 33, 41) if cplx else COLS):
+        Xm = Xd[:, :m].contiguous()
+        Ym = h2x.h2_matmul(A, Xm)
+        assert torch.equal(Ym, Y[:, :m]), m
+        out = torch.ones_like(Ym)
+        h2x.h2_matmul(A, Xm, alpha=2.0, beta=3.0, out=out)
+        assert torch.equal(out, 3.0 + 2.0 * Ym), m
+
+
+@pytest.mark.parametrize("leaf", [45, 64, 100])
+def test_fp64_many_leaves(leaf):
+    """17 to 32 columns on more than 1024 leaves above 32 points take two waves per leaf; the same bits
+    as the first columns of a wider product, which takes four."""
+    import paper_2509_17257_amd as h2x
+    n = 130000
+    A = h2x.H2Matrix(W.sphere_points(n, 730), ell=0.5, shift=1.0, eta=1.0, leaf=leaf, p=2)
+    assert (A.plan.C + 1) // 2 >= 1024
+    X = torch.from_numpy(W.rhs(n, 40, 731)).cuda()
+    Y = h2x.h2_matmul(A, X)
+    for m in (16, 17, 31, 32):
+        assert torch.equal(h2x.h2_matmul(A, X[:, :m].contiguous()), Y[:, :m]), m
