@@ -68,9 +68,6 @@ struct LeafCatLpArgs {
     Skip skip;
 };
 
-template <int NC>
-constexpr size_t leaf_cat_lp_red_bytes() { return sizeof(float) * 64 * (16 * NC + 1); }
-
 // NT row tiles from row i0 on (ic of these rows present) and NC column tiles.  The rounds are summed
 // in G groups (group r % G: two where the chunk has three or four row tiles, four below); of the GW
 // waves of these rows, wave g takes the groups g, g + GW, .. in turn.  The groups' partial tiles
