@@ -4,8 +4,9 @@
 // One wave works alone on a row cluster and a slab of 16 NJ columns: it loads NB consecutive
 // blocks of its list (row-major S_b, contiguous over the list) and their x_s into registers with
 // whole-line loads, one step ahead, puts them into its own stretch of LDS, and multiplies from
-// there with v_mfma_f64_16x16x4f64.  LDS operations of a wave complete in order, so a step needs
-// neither a barrier nor a second buffer.  The list's steps are cut into four consecutive parts
+// there with v_mfma_f64_16x16x4f64.  LDS operations of a wave complete in the order in which they
+// are issued and wave_sync keeps the compiler from changing it, so a step needs neither a
+// work-group barrier nor a second buffer.  The list's steps are cut into four consecutive parts
 // whose sums are added in order, either by the four waves of a work-group, a part each (SP = 4: a
 // quarter of the serial chain), or by one wave, part after part (SP = 1: four units to a
 // work-group).  So every launch shape gives the same bits, and a system solved in a batch those
@@ -126,8 +127,10 @@ __global__ __launch_bounds__(256) void k_coupling_small(
         for (int end = first + quarter;; end += quarter) {  // (SP = 4: one part)
             for (const int stop = min(end, last - 1); i < stop; ++i) {
                 store(i);
+                wave_sync();
                 load(i + 1);
                 multiply();
+                wave_sync();
             }
             if (SP > 1 || end >= last) break;
 #pragma unroll
@@ -139,6 +142,7 @@ __global__ __launch_bounds__(256) void k_coupling_small(
                 }
         }
         store(i);
+        wave_sync();
         multiply();
         if constexpr (SP == 1)
 #pragma unroll

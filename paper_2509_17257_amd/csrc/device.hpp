@@ -38,6 +38,15 @@ __device__ inline u32x2 buf_ld8(__amdgpu_buffer_rsrc_t r, uint32_t off) {
     return __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, POL);
 }
 
+// Orders the LDS accesses of one wave: what a lane stored before it is what another lane of the
+// wave loads after it, and the reverse.  The hardware completes a wave's LDS operations in issue
+// order, so this holds the compiler only and costs no instruction.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Tile choices of the matrix-core paths (0: the default rule), filled by the
 // autotuner per bucket of the column count: bucket b holds ceil(m / 16) = b + 1
 // for b < 4, bucket 4 anything wider.
