@@ -243,11 +243,12 @@ __global__ __launch_bounds__(256) void k_leaf_near(int k, int64_t m, const int32
                                                    const int64_t *__restrict__ near_off, const TN *__restrict__ N,
                                                    const double *__restrict__ X, int64_t ldx, double alpha,
                                                    double beta, double *__restrict__ Y, int64_t ldy, int tree_order,
-                                                   int near_t) {
+                                                   int near_t, Skip skip) {
     __shared__ Acc As[TR][TR + 1];
     __shared__ Acc Bs[TR][TC];
     const int32_t l = blockIdx.x;
     const int32_t t = leaves[l];
+    if (skip(t)) return;
     const int64_t j0 = (int64_t)blockIdx.y * TC;
     const int mc = (int)min<int64_t>(TC, m - j0);
     const int tid = threadIdx.x, rg = tid >> 5, j = tid & 31;
@@ -670,7 +671,7 @@ void matmul_gen_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alph
         hipLaunchKernelGGL((k_leaf_near<double, double, double>), dim3(dm.L, (unsigned)((m + TC - 1) / TC)), dim3(256), 0,
                            st, dm.k, m, dm.leaves, dm.first, dm.size, dm.perm, (const double *)dm.V, yh, ldh,
                            dm.near_ptr, dm.near_col, dm.near_off, (const double *)dm.N, X, ldx, alpha, beta, Y, ldy, to,
-                           dm.near_t);
+                           dm.near_t, sk);
     }
     mark(5);
     if (ev) (void)hipEventRecord(ev[6], st);
@@ -853,7 +854,7 @@ hipError_t matmul_lp(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     }
     hipLaunchKernelGGL((k_leaf_near<T, TN, Acc>), dim3(dm.L, gy), dim3(256), 0, st, dm.k, m, dm.leaves, dm.first,
                        dm.size, dm.perm, V, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off, (const TN *)dm.N, X, ldx,
-                       alpha, beta, Y, ldy, to, dm.near_t);
+                       alpha, beta, Y, ldy, to, dm.near_t, Skip{});
     mark(5);
     if (ev) (void)hipEventRecord(ev[6], st);
     return hipGetLastError();
