@@ -329,6 +329,15 @@ inline bool cat_two_waves(const DevMat &dm, int nc, int64_t slots) {
     return nc == 2 && slots >= 1024 && dm.max_leaf > 32;
 }
 
+// FP64 leaf stage as one contraction per leaf: the table of near rows and the partial tiles of 16 NC
+// columns fit in 64 KB of LDS, and X and one cluster's y-hat, read at 32-bit byte offsets, are
+// below 4 GiB
+inline bool cat_fits(const DevMat &dm, size_t table, int NC, int64_t ldxt, int64_t ldh) {
+    const size_t lim = ((size_t)1 << 32) / sizeof(double);
+    return table + mfma::leaf_cat_red_bytes(NC) + 64 <= 65536 && (size_t)dm.n * (size_t)ldxt < lim &&
+           (size_t)dm.k * (size_t)ldh < lim;
+}
+
 // All five stages on the matrix cores (FP64 operator, k = 64 or k <= 32).
 template <int NJ>
 void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alpha, const double *X, int64_t ldx,
@@ -370,9 +379,7 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     const size_t table = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
     const int cat_np = dm.cplx ? 1 : NP;  // complex operators: slabs of at most 32 real columns
     const size_t red = mfma::leaf_cat_red_bytes(2 * cat_np), cat_lds = std::max(table, red);
-    // (it reads the rows of X through a buffer resource: 32-bit byte offsets)
-    const bool cat_ok = table + red + 64 <= 65536 &&
-                        sizeof(double) * (size_t)dm.n * (size_t)ldxt < ((size_t)1 << 32);
+    const bool cat_ok = cat_fits(dm, table, 2 * cat_np, ldxt, ldh);
     const int kind = cfg.leaf_kind == 0 ? (cat_ok ? 3 : 1) : (cfg.leaf_kind == 3 && !cat_ok ? 1 : cfg.leaf_kind);
     const bool rows = kind == 2;
     const int cat_nc = cat_tiles(m, cat_np);
@@ -655,10 +662,8 @@ void matmul_gen_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alph
     const size_t table = sizeof(int32_t) * (size_t)std::max(1, dm.max_near_rows);
     const size_t red = mfma::leaf_cat_red_bytes(2 * NP), cat_lds = std::max(table, red);
     const unsigned gl = (unsigned)((m + 32 * NP - 1) / (32 * NP));
-    // one contraction per leaf where its table of near rows fits in LDS (and X in 32-bit byte
-    // offsets), else the generic tiles
-    if (table + red + 64 <= 65536 &&
-        sizeof(double) * (size_t)dm.n * (size_t)ldxt < ((size_t)1 << 32)) {
+    // one contraction per leaf where it can be, else the generic tiles
+    if (cat_fits(dm, table, 2 * NP, ldxt, ldh)) {
         const int64_t slots = (int64_t)8 * ((dm.L + 7) / 8) * gl;
         const mfma::LeafCatArgs a{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm,
                                   (const double *)dm.Vt, dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off,

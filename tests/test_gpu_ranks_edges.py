@@ -98,3 +98,20 @@ def test_other_kernels(p, leaf, m, kernel):
     S = A.coupling()
     A.set_coupling(2.0 * S)
     assert torch.equal(A.coupling(), 2.0 * S)
+
+
+def test_a_million_columns():
+    """2^20 and more columns at rank 512: a cluster's rows of y-hat take more than 4 GiB.  The first,
+    the middle and the last columns against the oracle."""
+    h2x = _h2x()
+    n, m, w = 200, (1 << 20) + 4096, 20
+    P = 0.1 * W.cube_points(n, 820)
+    P[n // 2:, 0] += 0.9
+    prm = dict(ell=0.5, shift=1.0, eta=1.0, leaf=n // 2, p=8)
+    A, o = h2x.H2Matrix(P, **prm), oracle.OracleH2(P, **prm)
+    assert A.plan.n_adm == 2
+    X = torch.randn(n, m, dtype=torch.float64, device="cuda", generator=torch.Generator(device="cuda").manual_seed(821))
+    Y = h2x.h2_matmul(A, X)
+    for a in (0, m // 2, m - w):
+        ref = o.matmul(X[:, a:a + w].cpu().numpy())
+        assert _rel(Y[:, a:a + w].cpu().numpy(), ref) <= 1e-12, a
