@@ -448,7 +448,8 @@ hipError_t fill_typed(const DevMat &dm, hipStream_t st) {
         hipLaunchKernelGGL(k_fill_V<T>, dim3(dm.L), dim3(256), 0, st, dm.p, dm.leaves, dm.first, dm.size, dm.pts,
                            dm.nodes, (T *)dm.V, (T *)dm.Vt, dm.vt_off);
     if (dm.C > 1) {
-        hipLaunchKernelGGL(k_fill_E<T>, dim3(dm.C - 1), dim3(256), 0, st, dm.p, dm.parent, dm.nodes, (T *)dm.E);
+        if (dm.E)
+            hipLaunchKernelGGL(k_fill_E<T>, dim3(dm.C - 1), dim3(256), 0, st, dm.p, dm.parent, dm.nodes, (T *)dm.E);
         const int64_t nf = (int64_t)dm.C * 3 * dm.p * dm.p;
         hipLaunchKernelGGL(k_fill_E1, dim3((unsigned)((nf + 255) / 256)), dim3(256), 0, st, dm.C, dm.p, dm.parent,
                            dm.nodes, dm.E1);
@@ -532,7 +533,8 @@ size_t mat_layout(const Plan &P, h2x_prec storage, DevMat *dm, char *base) {
     const size_t es = storage == H2X_F64 ? 8 : (storage == H2X_F32 ? 4 : 2);
     const size_t ens = storage == H2X_F64 ? 8 : 4;
     d.V = carve<char>(cur, base, es * (size_t)n * k);
-    d.E = carve<char>(cur, base, es * (size_t)C * k * k);
+    // (the transfer passes of the higher FP64 ranks read the one-dimensional factors only)
+    d.E = d.gk ? nullptr : carve<char>(cur, base, es * (size_t)C * k * k);
     d.E1 = carve<double>(cur, base, 3 * (size_t)C * P.p * P.p);
     // complex kernel: a real and an imaginary plane of S and N (V and E stay real)
     d.cplx = (P.nsys() == 1 && P.prm.kernel == H2X_KERNEL_HELMHOLTZ) ? 1 : 0;
