@@ -13,9 +13,11 @@
 // 64 x 1152 terms per column.
 //
 // Work-group: four waves for one (leaf, slab of 16 NC columns).  Chunks of up to 32 rows of a leaf
-// are one row group and the waves split the rounds (wave w takes rounds w, w + 4, ...); larger
-// chunks are two row groups of two tiles, each split over two waves (64 columns and three row
-// tiles: two column halves).  With two waves per work-group each takes every second round for all
+// are one row group (of one tile up to 16 rows) and the waves split the rounds (wave w takes
+// rounds w, w + 4, ...); larger chunks are two row groups of two tiles, or, for three row tiles
+// and an even NC, two column halves, each split over two waves (two tiles throughout, present or
+// not: leaves of 16, 64 columns, cube of 65536 leaf stage 462 against 319 us; leaves of up to 75, 32
+// columns 458 against 424).  With two waves per work-group each takes every second round for all
 // rows.  The partial tiles are added in LDS in wave order (a fixed order, the same for every form:
 // the result is reproducible and does not depend on the form).  Complex operators: every wave
 // all rows of every fourth round.  One or two further rounds of
@@ -55,7 +57,7 @@ template <int NC, int NT>
 struct CatRound {
     dbl2c a[NC / 2 + 1][4];  // [column pair p][k-step u]: columns 32p + 2 (l % 16) + {0, 1}
     double c[4];             // [k-step u], NC odd: column 16 (NC - 1) + l % 16
-    dbl2c b[NT / 2][4];      // [row pair q][k-step u]: rows 32q + 2 (l % 16) + {0, 1}
+    dbl2c b[NT / 2 + 1][4];  // [row pair q][k-step u]: rows 32q + 2 (l % 16) + {0, 1}
     double d[4];             // [k-step u], NT odd: row 16 (NT - 1) + l % 16
 };
 
@@ -122,7 +124,7 @@ __device__ inline void leaf_cat_chunk(const LeafCatArgs &a, int g, int lr, int l
     // (row lengths are even: a pair stays inside its row; the blocks of a leaf are below 4 GiB, as
     // their table fits in LDS)
     const uint32_t len = (uint32_t)nt2;
-    uint32_t row[NT / 2];
+    uint32_t row[NT / 2 + 1];
 #pragma unroll
     for (int q = 0; q < NT / 2; ++q) row[q] = (uint32_t)(i0 + min(32 * q + 2 * lr, (ic - 1) & ~1));
     const uint32_t rs = (uint32_t)(i0 + min(16 * (NT - 1) + lr, ic - 1));
@@ -254,8 +256,8 @@ template <int NC, int NW, bool CPX>
 __device__ inline void leaf_cat_slab(int32_t l, int64_t j0, const LeafCatArgs &a, double *red) {
     constexpr int MC = 16 * NC, LDR = MC + 1;
     int32_t *xrow = (int32_t *)red;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, lr = lane & 15,
-              lq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
     const int32_t t = a.leaves[l];
     if (a.skip(t)) return;
     const int nt = a.size[t];
@@ -278,11 +280,17 @@ __device__ inline void leaf_cat_slab(int32_t l, int64_t j0, const LeafCatArgs &a
                 leaf_cat_chunk<NC, 3, 4, 4, LDR, true>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
             else
                 leaf_cat_chunk<NC, 4, 4, 4, LDR, true>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
-        } else if (ic <= 32)
+        } else if (ic <= 16)
+            leaf_cat_chunk<NC, 1, 4, NW, LDR, CPX>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+        else if (ic <= 32)
             leaf_cat_chunk<NC, 2, 4, NW, LDR, CPX>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
-        else if (NW == 4 && NC == 4 && ic <= 48)  // two waves per 32 columns: equal work for three row tiles
-            leaf_cat_chunk<2, 3, 2, 2, LDR, CPX>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0 + 32 * (w >> 1),
-                                                 max(xc - 32 * (w >> 1), 0), xrow, red + 32 * (w >> 1));
+        else if (NW == 4 && NC % 2 == 0 && ic <= 48 && mc > 8 * NC) {
+            // two waves per column half: equal work for three row tiles
+            constexpr int HC = NC > 1 ? NC / 2 : 1;
+            const int ch = 16 * HC * (w >> 1);
+            leaf_cat_chunk<HC, 3, 2, 2, LDR, CPX>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0 + ch, xc - ch, xrow,
+                                                  red + ch);
+        }
         else if (NW == 4)  // two waves per 32 rows
             leaf_cat_chunk<NC, 2, 2, 2, LDR, CPX>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0 + 32 * (w >> 1),
                                                   w < 2 ? 32 : ic - 32, j0, xc, xrow, red + (w >> 1) * 32 * LDR);

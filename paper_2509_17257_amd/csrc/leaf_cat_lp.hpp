@@ -12,11 +12,11 @@
 //
 // Work-group: two or four waves for one (leaf, slab of 16 NC columns).  Two waves each take every
 // second round for all row tiles of a 64-row chunk and all column tiles, so every operand is loaded
-// once per work-group; four waves split chunks above 32 rows into two row groups (each loads the
-// rows of X for itself), so that few leaves still fill the chip.  The sums are the same bit for
-// bit.  Bound by the FP32 matrix cores (65 % busy) and the loads that feed them.  Slabs of 32 or
-// 64 columns spent up to a quarter of the products on padding and row groups 22 GB of cache
-// traffic where 13 do: 45 columns, n = 99991, BF16 basis, leaf stage 1029 -> 790 us; 64 columns,
+// once per work-group; four waves split chunks above 32 rows into two row groups or, for three row
+// tiles and an even NC, two column halves (each loads one operand for itself), so that few leaves
+// still fill the chip.  The sums are the same bit for bit.  Bound by the FP32 matrix cores and the
+// loads that feed them.  Slabs of 32 or 64 columns spent up to a quarter of the products on padding
+// and row groups 22 GB of cache traffic where 13 do: 45 columns, n = 99991, BF16 basis, leaf stage 1029 -> 790 us; 64 columns,
 // n = 262144, FP32 2330 -> 2150 us.  Registers allow two waves per SIMD and one round of
 // loads ahead; two rounds ahead spill (5 x slower), half rounds three ahead are 1 % slower.  The
 // row table and the partial tiles take the same LDS (beside each other: + 8 % of a product with
@@ -38,7 +38,7 @@ template <int NC, int NT>
 struct CatRoundLp {
     flt2 a[NC / 2 + 1][4];  // [column pair p][k-step u]: columns 32p + 2 (l % 16) + {0, 1}
     float c[4];             // [k-step u], NC odd: column 16 (NC - 1) + l % 16
-    flt2 b[NT / 2][4];      // [row pair q][k-step u]: rows 32q + 2 (l % 16) + {0, 1}
+    flt2 b[NT / 2 + 1][4];  // [row pair q][k-step u]: rows 32q + 2 (l % 16) + {0, 1}
     float d[4];             // [k-step u], NT odd: row 16 (NT - 1) + l % 16
 };
 
@@ -72,15 +72,15 @@ struct LeafCatLpArgs {
 // in G groups (group r % G: two where the chunk has three or four row tiles, four below); of the GW
 // waves of these rows, wave g takes the groups g, g + GW, .. in turn.  The groups' partial tiles
 // are added in LDS in order (red: their first row).
-template <int NC, int NT, int G, int GW, typename TV>
+template <int NC, int NT, int G, int GW, int LDR, typename TV>
 __device__ inline void leaf_cat_lp_chunk(const LeafCatLpArgs &a, int g, int lr, int lq, int32_t t, const float *nb,
                                          const TV *vb, int32_t rn, int64_t nt2, int i0, int ic, int64_t j0, int xc,
                                          const int32_t *xrow, float *red) {
-    constexpr int NA = G / GW, LDR = 16 * NC + 1, NPR = NC / 2;
+    constexpr int NA = G / GW, NPR = NC / 2;
     const int k = a.k;
     const int RN = (rn + 15) >> 4, RT = RN + ((k + 15) >> 4);
     // (row lengths are even: a pair stays inside its row)
-    uint32_t row[NT / 2];
+    uint32_t row[NT / 2 + 1];
 #pragma unroll
     for (int q = 0; q < NT / 2; ++q) row[q] = (uint32_t)(i0 + min(32 * q + 2 * lr, (ic - 1) & ~1));
     const uint32_t rs = (uint32_t)(i0 + min(16 * (NT - 1) + lr, ic - 1));
@@ -151,11 +151,11 @@ __device__ inline void leaf_cat_lp_chunk(const LeafCatLpArgs &a, int g, int lr, 
 
     if (g < RT) {
         const int last = g + ((RT - 1 - g) / GW) * GW;  // the wave's last round
-        CatRoundLp<NC, NT> s0, s1;
         int r = g;
-        load(r, s0);
         // two register sets in turn, loaded one round ahead of their use (a round past the last
         // re-reads that one, which the cache serves)
+        CatRoundLp<NC, NT> s0, s1;
+        load(r, s0);
         for (;;) {
             load(min(r + GW, last), s1);
             multiply(r, s0, acc[0]);
@@ -221,15 +221,23 @@ __global__ __launch_bounds__(64 * NW, 2) void k_leaf_cat_lp(LeafCatLpArgs a) {
         const int32_t rn =
             nnear > 0 ? mfma::cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size) : 0;
         const int ic = min(64, nt - i0);
-        if (ic <= 32)
-            leaf_cat_lp_chunk<NC, 2, 4, NW>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
-        else if (NW == 4)  // two waves per 32 rows
-            leaf_cat_lp_chunk<NC, 2, 2, 2>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0 + 32 * (w >> 1),
-                                           w < 2 ? 32 : ic - 32, j0, xc, xrow, red + (w >> 1) * 32 * LDR);
+        if (ic <= 16)
+            leaf_cat_lp_chunk<NC, 1, 4, NW, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+        else if (ic <= 32)
+            leaf_cat_lp_chunk<NC, 2, 4, NW, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+        else if (NW == 4 && NC % 2 == 0 && ic <= 48 && mc > 8 * NC) {
+            // two waves per column half: equal work for three row tiles
+            constexpr int HC = NC > 1 ? NC / 2 : 1;
+            const int ch = 16 * HC * (w >> 1);
+            leaf_cat_lp_chunk<HC, 3, 2, 2, LDR>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0 + ch, xc - ch,
+                                                xrow, red + ch);
+        } else if (NW == 4)  // two waves per 32 rows
+            leaf_cat_lp_chunk<NC, 2, 2, 2, LDR>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0 + 32 * (w >> 1),
+                                                w < 2 ? 32 : ic - 32, j0, xc, xrow, red + (w >> 1) * 32 * LDR);
         else if (ic <= 48)
-            leaf_cat_lp_chunk<NC, 3, 2, 2>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+            leaf_cat_lp_chunk<NC, 3, 2, 2, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
         else
-            leaf_cat_lp_chunk<NC, 4, 2, 2>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+            leaf_cat_lp_chunk<NC, 4, 2, 2, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
         for (int x = threadIdx.x; x < ic * MC; x += 64 * NW) {
             const int i = x / MC, j = x - i * MC;
             if (j < mc) {

@@ -319,14 +319,14 @@ inline int64_t even_ld(int64_t m) { return m + (m & 1); }
 // leaf stage: 16-column tiles of a slab of at most 32 NP columns, narrow for few columns
 inline int cat_tiles(int64_t m, int NP) { return (int)std::min<int64_t>(2 * NP, (m + 15) / 16); }
 
-// Two waves per (leaf, slab) load every operand once; four have two row groups with the rows of X
-// loaded twice, but half the serial rounds.  Two win for 17 to 32 columns where the leaves fill the
-// chip (1024 such groups fit at a time) and have three or four row tiles: n = 65536, m = 32 780 (two) /
-// 787 us (four) per product, 16 merged systems 1535 / 1590 us.  At one tile of columns the loads
-// of X are few: m = 1 610 / 605 us; few leaves want the waves: n = 32768, leaf 128, m = 16
-// 706 / 671 us; above 32 columns the sums of two waves do not fit their registers.
+// Two waves per (leaf, slab) load every operand once; four have two row groups (or column halves)
+// that load one operand twice, but half the serial rounds.  Two win for 17 to 32 columns where they
+// fill the chip twice (1024 such groups fit at a time) and have three or four row tiles: m = 32,
+// n = 65536, 1543 leaves 789 (two) / 781 us (four) per product, n = 131072 1554 / 1576, n = 262144
+// 3088 / 3147.  At one tile of columns the loads of X are few: n = 65536, m = 1 610 / 605 us; above
+// 32 columns the sums of two waves do not fit their registers.
 inline bool cat_two_waves(const DevMat &dm, int nc, int64_t slots) {
-    return nc == 2 && slots >= 1024 && dm.max_leaf > 32;
+    return nc == 2 && slots >= 2048 && dm.max_leaf > 32;
 }
 
 // FP64 leaf stage as one contraction per leaf: the table of near rows and the partial tiles of 16 NC
