@@ -17,6 +17,7 @@
 #include "device.hpp"
 #include "coupling_lp.hpp"
 #include "coupling_rows.hpp"
+#include "launch_rules.hpp"
 #include "leaf_cat.hpp"
 #include "leaf_cat_lp.hpp"
 #include "leaf_lp.hpp"
@@ -319,14 +320,10 @@ inline int64_t even_ld(int64_t m) { return m + (m & 1); }
 // leaf stage: 16-column tiles of a slab of at most 32 NP columns, narrow for few columns
 inline int cat_tiles(int64_t m, int NP) { return (int)std::min<int64_t>(2 * NP, (m + 15) / 16); }
 
-// Two waves per (leaf, slab) load every operand once; four have two row groups (or column halves)
-// that load one operand twice, but half the serial rounds.  Two win for 17 to 32 columns where they
-// fill the chip twice (1024 such groups fit at a time) and have three or four row tiles: m = 32,
-// n = 65536, 1543 leaves 789 (two) / 781 us (four) per product, n = 131072 1554 / 1576, n = 262144
-// 3088 / 3147.  At one tile of columns the loads of X are few: n = 65536, m = 1 610 / 605 us; above
-// 32 columns the sums of two waves do not fit their registers.
-inline bool cat_two_waves(const DevMat &dm, int nc, int64_t slots) {
-    return nc == 2 && slots >= 2048 && dm.max_leaf > 32;
+// (the sums of two waves fit their registers at up to 32 columns; at one tile of columns the loads
+// of X are few: n = 65536, m = 1 610 us with two waves, 605 with four)
+inline bool cat_two_waves(const DevMat &dm, int nc, int64_t slots, size_t lds) {
+    return nc == 2 && leaf_two_waves(slots, dm.max_leaf, lds);
 }
 
 // FP64 leaf stage as one contraction per leaf: the table of near rows and the partial tiles of 16 NC
@@ -384,7 +381,7 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     const bool rows = kind == 2;
     const int cat_nc = cat_tiles(m, cat_np);
     const int64_t cat_slots = (int64_t)8 * ((dm.L + 7) / 8) * ((m + 16 * cat_nc - 1) / (16 * cat_nc));
-    const bool cat_two = cat_two_waves(dm, cat_nc, cat_slots);
+    const bool cat_two = cat_two_waves(dm, cat_nc, cat_slots, cat_lds);
     auto cat_args = [&](double b, int basis, int near) {
         return mfma::LeafCatArgs{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm, (const double *)dm.Vt,
                                  dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off, (const double *)dm.N, Xt,
@@ -669,7 +666,7 @@ void matmul_gen_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alph
                                   (const double *)dm.Vt, dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off,
                                   (const double *)dm.N, Xt, ldxt, alpha, beta, Y, ldy, to, 1, 1, sk, 0};
         const int nc = cat_tiles(m, NP);
-        mfma::leaf_cat_kernel(nc, cat_two_waves(dm, nc, slots), false, [&](auto kern, int threads) {
+        mfma::leaf_cat_kernel(nc, cat_two_waves(dm, nc, slots, cat_lds), false, [&](auto kern, int threads) {
             hipLaunchKernelGGL(kern, dim3((unsigned)slots), dim3(threads), cat_lds, st, a, (int64_t)0, slots);
         });
     } else {
@@ -823,12 +820,7 @@ hipError_t matmul_lp(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
                                       dm.Vt, dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off,
                                       (const float *)dm.N, xt, ldxt, alpha, beta, Y, ldy, to, rb, sk};
             const unsigned grid = gl8 * (unsigned)((m + 16 * NC - 1) / (16 * NC));
-            // Two waves per (leaf, slab) hold every operand once and win where they fill the chip more
-            // than twice (1024 fit at a time) and hold three or four row tiles; else four waves:
-            // n = 262144, 64 columns, FP32, 6002 leaves 8320 (two) / 8590 us (four) per product,
-            // n = 130000 3037 leaves 1436 / 1454, n = 65536 1543 leaves 770 / 765, n = 16000 362
-            // leaves 818 / 659; leaves of up to 32 rows, 4301 of them 2435 / 2346.
-            const bool two = grid >= 2048 && dm.max_leaf > 32;
+            const bool two = leaf_two_waves(grid, dm.max_leaf, cat_lds);
             auto go = [&](auto n) {
                 if (two)
                     hipLaunchKernelGGL((lp::k_leaf_cat_lp<decltype(n)::value, 2, T>), dim3(grid), dim3(128), cat_lds, st,
