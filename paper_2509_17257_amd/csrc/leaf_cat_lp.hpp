@@ -17,9 +17,10 @@
 // still fill the chip.  The sums are the same bit for bit.  Bound by the FP32 matrix cores and the
 // loads that feed them.  Slabs of 32 or 64 columns spent up to a quarter of the products on padding
 // and row groups 22 GB of cache traffic where 13 do: 45 columns, n = 99991, BF16 basis, leaf stage 1029 -> 790 us; 64 columns,
-// n = 262144, FP32 2330 -> 2150 us.  Registers allow two waves per SIMD and one round of
-// loads ahead; two rounds ahead spill (5 x slower), half rounds three ahead are 1 % slower.  The
-// row table and the partial tiles take the same LDS (beside each other: + 8 % of a product with
+// n = 262144, FP32 2330 -> 2150 us.  Above four tiles per wave the registers allow two waves per
+// SIMD and one round of loads ahead (two rounds ahead spill: 5 x slower, half rounds three ahead are
+// 1 % slower); up to four tiles of a chunk above 32 rows two rounds fly (leaves of up to 100 points, 32
+// columns, BF16: leaf stage 335 -> 315 us).  The row table and the partial tiles take the same LDS (beside each other: + 8 % of a product with
 // tables of 30 KB).
 //
 // Lane layout of v_mfma_f32_16x16x4f32 (A: 16 x 4, B: 4 x 16, D: 16 x 16): lane l holds
@@ -152,17 +153,34 @@ __device__ inline void leaf_cat_lp_chunk(const LeafCatLpArgs &a, int g, int lr, 
     if (g < RT) {
         const int last = g + ((RT - 1 - g) / GW) * GW;  // the wave's last round
         int r = g;
-        // two register sets in turn, loaded one round ahead of their use (a round past the last
-        // re-reads that one, which the cache serves)
-        CatRoundLp<NC, NT> s0, s1;
-        load(r, s0);
-        for (;;) {
+        if constexpr (NA == 1 && G == 2 && NC * NT <= 4) {
+            // three register sets in turn; a set is loaded two rounds ahead of its use (a round past
+            // the last re-reads that one, which the cache serves)
+            CatRoundLp<NC, NT> s0, s1, s2;
+            load(r, s0);
             load(min(r + GW, last), s1);
-            multiply(r, s0, acc[0]);
-            if ((r += GW) > last) break;
-            load(min(r + GW, last), s0);
-            multiply(r, s1, acc[NA - 1]);
-            if ((r += GW) > last) break;
+            for (;;) {
+                load(min(r + 2 * GW, last), s2);
+                multiply(r, s0, acc[0]);
+                if ((r += GW) > last) break;
+                load(min(r + 2 * GW, last), s0);
+                multiply(r, s1, acc[0]);
+                if ((r += GW) > last) break;
+                load(min(r + 2 * GW, last), s1);
+                multiply(r, s2, acc[0]);
+                if ((r += GW) > last) break;
+            }
+        } else {  // two sets, one round ahead
+            CatRoundLp<NC, NT> s0, s1;
+            load(r, s0);
+            for (;;) {
+                load(min(r + GW, last), s1);
+                multiply(r, s0, acc[0]);
+                if ((r += GW) > last) break;
+                load(min(r + GW, last), s0);
+                multiply(r, s1, acc[NA - 1]);
+                if ((r += GW) > last) break;
+            }
         }
     }
     __syncthreads();  // the row table was read for the last time: its LDS takes the partial tiles
@@ -192,7 +210,7 @@ __device__ inline void leaf_cat_lp_chunk(const LeafCatLpArgs &a, int g, int lr, 
 // one (leaf, column slab) per work-group, mapped to XCDs as in the FP64 form (slot & 7 is the
 // XCD, whose leaves form one contiguous eighth of the launch order; the slabs of one leaf are
 // consecutive slots of one XCD).  Dynamic LDS: the near-row table, then the partial tiles.
-template <int NC, int NW, typename TV>
+template <int NC, int NW, int ROWS, typename TV>
 __global__ __launch_bounds__(64 * NW, 2) void k_leaf_cat_lp(LeafCatLpArgs a) {
     constexpr int MC = 16 * NC, LDR = MC + 1;
     extern __shared__ float red[];
@@ -223,21 +241,23 @@ __global__ __launch_bounds__(64 * NW, 2) void k_leaf_cat_lp(LeafCatLpArgs a) {
         const int ic = min(64, nt - i0);
         if (ic <= 16)
             leaf_cat_lp_chunk<NC, 1, 4, NW, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
-        else if (ic <= 32)
+        else if (ROWS <= 32 || ic <= 32)
             leaf_cat_lp_chunk<NC, 2, 4, NW, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
-        else if (NW == 4 && NC % 2 == 0 && ic <= 48 && mc > 8 * NC) {
-            // two waves per column half: equal work for three row tiles
-            constexpr int HC = NC > 1 ? NC / 2 : 1;
-            const int ch = 16 * HC * (w >> 1);
-            leaf_cat_lp_chunk<HC, 3, 2, 2, LDR>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0 + ch, xc - ch,
-                                                xrow, red + ch);
-        } else if (NW == 4)  // two waves per 32 rows
-            leaf_cat_lp_chunk<NC, 2, 2, 2, LDR>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0 + 32 * (w >> 1),
-                                                w < 2 ? 32 : ic - 32, j0, xc, xrow, red + (w >> 1) * 32 * LDR);
-        else if (ic <= 48)
-            leaf_cat_lp_chunk<NC, 3, 2, 2, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
-        else
-            leaf_cat_lp_chunk<NC, 4, 2, 2, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+        else if constexpr (ROWS > 32) {
+            if (NW == 4 && NC % 2 == 0 && ic <= 48 && mc > 8 * NC) {
+                // two waves per column half: equal work for three row tiles
+                constexpr int HC = NC > 1 ? NC / 2 : 1;
+                const int ch = 16 * HC * (w >> 1);
+                leaf_cat_lp_chunk<HC, 3, 2, 2, LDR>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0 + ch, xc - ch,
+                                                    xrow, red + ch);
+            } else if (NW == 4)  // two waves per 32 rows
+                leaf_cat_lp_chunk<NC, 2, 2, 2, LDR>(a, w & 1, lr, lq, t, nb, vb, rn, nt2, i0 + 32 * (w >> 1),
+                                                    w < 2 ? 32 : ic - 32, j0, xc, xrow, red + (w >> 1) * 32 * LDR);
+            else if (ic <= 48)
+                leaf_cat_lp_chunk<NC, 3, 2, 2, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+            else
+                leaf_cat_lp_chunk<NC, 4, 2, 2, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
+        }
         for (int x = threadIdx.x; x < ic * MC; x += 64 * NW) {
             const int i = x / MC, j = x - i * MC;
             if (j < mc) {
