@@ -65,12 +65,13 @@ struct CatRound {
 // blocks' offsets: block q starts at near row (off_q - off_q0) / |t|_even)
 __device__ inline int32_t cat_build_rows(int32_t *xrow, int64_t q0, int nnear, int64_t nt2,
                                          const int32_t *__restrict__ near_col, const int64_t *__restrict__ near_off,
-                                         const int32_t *__restrict__ first, const int32_t *__restrict__ size) {
+                                         const int32_t *__restrict__ first, const int32_t *__restrict__ size,
+                                         int tid) {
     __shared__ int32_t rn;
     const int64_t base = near_off[q0];
-    if (threadIdx.x == 0) rn = 0;
+    if (tid == 0) rn = 0;
     __syncthreads();
-    for (int x = threadIdx.x; x < nnear; x += blockDim.x) {
+    for (int x = tid; x < nnear; x += blockDim.x) {
         const int32_t s = near_col[q0 + x];
         const int32_t off = (int32_t)((near_off[q0 + x] - base) / nt2), fs = first[s], ks = size[s];
         for (int c = 0; c < ks; ++c) xrow[off + c] = fs + c;
@@ -253,11 +254,11 @@ __device__ inline void leaf_cat_chunk(const LeafCatArgs &a, int g, int lr, int l
 
 // columns j0..j0 + 16 NC - 1 of leaf l by NW waves; red: the dynamic LDS
 template <int NC, int NW, bool CPX>
-__device__ inline void leaf_cat_slab(int32_t l, int64_t j0, const LeafCatArgs &a, double *red) {
+__device__ inline void leaf_cat_slab(int32_t l, int64_t j0, const LeafCatArgs &a, double *red, int tid) {
     constexpr int MC = 16 * NC, LDR = MC + 1;
     int32_t *xrow = (int32_t *)red;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+    const int lane = tid & 63, lr = lane & 15, lq = lane >> 4;
     const int32_t t = a.leaves[l];
     if (a.skip(t)) return;
     const int nt = a.size[t];
@@ -271,7 +272,7 @@ __device__ inline void leaf_cat_slab(int32_t l, int64_t j0, const LeafCatArgs &a
 
     for (int i0 = 0; i0 < nt; i0 += 64) {
         const int32_t rn =
-            nnear > 0 ? cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size) : 0;
+            nnear > 0 ? cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size, tid) : 0;
         const int ic = min(64, nt - i0);
         if constexpr (CPX) {  // four groups: the sums are twice as long
             if (ic <= 32)
@@ -300,7 +301,7 @@ __device__ inline void leaf_cat_slab(int32_t l, int64_t j0, const LeafCatArgs &a
             else
                 leaf_cat_chunk<NC, 4, 2, 2, LDR, CPX>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
         }
-        for (int x = threadIdx.x; x < ic * MC; x += 64 * NW) {
+        for (int x = tid; x < ic * MC; x += 64 * NW) {
             const int i = x / MC, j = x - i * MC;
             if (j < mc) {
                 int64_t row = r0 + i0 + i;
@@ -326,12 +327,16 @@ __device__ inline void leaf_cat_slot(int64_t slot, const LeafCatArgs &a, double 
     if (pos >= a.L) return;
     const int32_t l = a.order[pos];
     const int64_t j0 = (qx % nslab) * (16 * NC);
+    int tid = threadIdx.x;
+    // 64 columns: the thread's number is opaque in each slot, as the offsets of every form would else be
+    // computed before the loop over slots and held across it (20 registers spilled)
+    if (NC == 4) asm volatile("" : "+v"(tid));
     if (NC == 4 && a.m - j0 <= 32)
-        leaf_cat_slab<2, NW, CPX>(l, j0, a, red);
+        leaf_cat_slab<2, NW, CPX>(l, j0, a, red, tid);
     else if (NC == 4 && a.m - j0 <= 48)
-        leaf_cat_slab<3, NW, CPX>(l, j0, a, red);
+        leaf_cat_slab<3, NW, CPX>(l, j0, a, red, tid);
     else
-        leaf_cat_slab<NC, NW, CPX>(l, j0, a, red);
+        leaf_cat_slab<NC, NW, CPX>(l, j0, a, red, tid);
 }
 
 // ---- the near-field term of d ell ----
@@ -377,7 +382,8 @@ __device__ inline double leaf_dell_slot(int64_t slot, const LeafCatArgs &a, cons
     const int mc = (int)min<int64_t>(MC, a.m - j0);
     const int64_t q0 = a.near_ptr[l];
     const int nnear = (int)(a.near_ptr[l + 1] - q0);
-    const int32_t rn = nnear > 0 ? cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size) : 0;
+    const int32_t rn =
+        nnear > 0 ? cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size, threadIdx.x) : 0;
     const int RT = (rn + 15) >> 4;
     const double *nb = nnear > 0 ? a.Nt + a.near_off[q0] : a.Nt;
     const int xc = (mc - 1) & ~1;

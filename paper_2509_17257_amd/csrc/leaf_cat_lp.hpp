@@ -237,7 +237,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_leaf_cat_lp(LeafCatLpArgs a) {
     const int xc = (mc - 1) & ~1;  // last even column offset of the slab
     for (int i0 = 0; i0 < nt; i0 += 64) {
         const int32_t rn =
-            nnear > 0 ? mfma::cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size) : 0;
+            nnear > 0 ? mfma::cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size, threadIdx.x)
+                      : 0;
         const int ic = min(64, nt - i0);
         if (ic <= 16)
             leaf_cat_lp_chunk<NC, 1, 4, NW, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
