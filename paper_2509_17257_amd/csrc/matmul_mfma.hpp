@@ -152,12 +152,11 @@ __device__ inline void coupling64(int32_t t, int64_t j0, int mc, const int64_t *
         // selects) and the last block is peeled off, so the compiler's wait counters are
         // exact: the MFMAs wait only for the current block, never for the prefetch
         int left = quarter;
-        for (int64_t b = b0; b + 1 < b1; ++b) {
-            const int buf = (int)((b - b0) & 1);
-            load_x(adm_col[b + 1]);
-            load_s(b + 1, sn);
-            multiply(buf);
-            // (rarely taken, kept out of line; nested loops or selects cost the 32-column form 15 %)
+        // the end of a part (rarely taken, kept out of line; nested loops or selects cost the 32-column
+        // form 15 %): after the products, or at 32 columns behind the barrier, as a branch between
+        // products and stores makes the compiler issue that form's loads late (n = 65536, 32 columns
+        // 0.494 -> 0.483 ms; behind the barrier 48 columns on a cube 1.30 -> 1.41 ms)
+        auto flush = [&]() {
             if (__builtin_expect(--left == 0, 0)) {
                 left = quarter;
 #pragma unroll
@@ -166,10 +165,18 @@ __device__ inline void coupling64(int32_t t, int64_t j0, int mc, const int64_t *
                     acc[J] = dbl4{0.0, 0.0, 0.0, 0.0};
                 }
             }
+        };
+        for (int64_t b = b0; b + 1 < b1; ++b) {
+            const int buf = (int)((b - b0) & 1);
+            load_x(adm_col[b + 1]);
+            load_s(b + 1, sn);
+            multiply(buf);
+            if constexpr (NJ != 2) flush();
             store_x(buf ^ 1);
 #pragma unroll
             for (int kk2 = 0; kk2 < 8; ++kk2) sa[kk2] = sn[kk2];
             __syncthreads();
+            if constexpr (NJ == 2) flush();
         }
         multiply((int)((b1 - 1 - b0) & 1));
 #pragma unroll
