@@ -220,6 +220,7 @@ __device__ inline double exp_kernel(double r2, double ell, double ie) {
 // (cptr given), the block (t, s) with t < s also writes the transposed block (s, t), entry i of
 // column list t for entry i of row list t, and (s, t) writes nothing.  In layout 1 a thread then
 // holds the 2 x 2 patch {nu, nu + 4} x {mu, mu + 4}, two 16-byte stores for either block.
+// P <= 2: launched with 64 threads, a thread per entry.
 // Bound by the FP64 vector instructions of the square root and the exponential (about 65 an
 // entry) and by the stores: 5.57 GB of rank-64 FP64 blocks in 1.10 ms (5.0 TB/s); 1.57 ms without
 // the transposed blocks, 2.80 ms with nodes, divisions and 8-byte stores per entry.
@@ -319,8 +320,13 @@ __global__ __launch_bounds__(256) void k_fill_S_exp(double ell, const int32_t *_
 // Bound by the evaluation (about 130 vector instructions an entry) at four work-groups per CU:
 // 1.2 GB of FP64 blocks of 43 points in 0.50 ms; 0.60 ms without the transposed blocks, 0.69 ms
 // with 64-bit divisions and 8-byte stores a block row apart.
-template <typename TN>
-__global__ __launch_bounds__(256) void k_fill_N(int kernel, double ell, double shift, double npts, int64_t q0,
+// TA: points per side of a tile: 64, or 32 or 16 (with 64 threads) where no leaf is larger.  A block of
+// 8 points in a 64-wide tile took the LDS of a large one and 256 threads: refill of both S and N,
+// n = 65536, leaves of 8, rank 1 0.40 ms before tiles, 0.60 with 64, 0.24 with 16; leaves of 16,
+// rank 8 0.31 / 0.42 / 0.18; leaves of 24 0.28 / 0.33 / 0.28.
+template <typename TN, int TA>
+__global__ __launch_bounds__(TA > 16 ? 256 : 64) void k_fill_N(
+                                                int kernel, double ell, double shift, double npts, int64_t q0,
                                                 const int32_t *__restrict__ near_row,
                                                 const int32_t *__restrict__ near_col,
                                                 const int64_t *__restrict__ near_off,
@@ -329,7 +335,7 @@ __global__ __launch_bounds__(256) void k_fill_N(int kernel, double ell, double s
                                                 int64_t n_plane, const int32_t *__restrict__ leaf_of,
                                                 const int64_t *__restrict__ ptr, const int64_t *__restrict__ cptr,
                                                 const int64_t *__restrict__ cblk) {
-    constexpr int TA = 64, TL = 64;
+    constexpr int TL = TA, TH = TA > 16 ? 256 : 64;  // threads
     __shared__ TN tile[TL * (TA + 1)];
     __shared__ double pts_a[3][TA], pts_c[3][TL];  // the tile's points
     const int64_t q = q0 + blockIdx.x;
@@ -355,7 +361,7 @@ __global__ __launch_bounds__(256) void k_fill_N(int kernel, double ell, double s
             if ((int)threadIdx.x < 3 * na) pts_a[threadIdx.x % 3][threadIdx.x / 3] = pa[3 * (int64_t)a0 + threadIdx.x];
             if ((int)threadIdx.x < 3 * nc) pts_c[threadIdx.x % 3][threadIdx.x / 3] = pc[3 * (int64_t)c0 + threadIdx.x];
             __syncthreads();
-            for (int e = threadIdx.x; e < na * nc; e += 256) {
+            for (int e = threadIdx.x; e < na * nc; e += TH) {
                 const int a = (int)((e + 0.5f) * inv), c = e - a * nc;  // exact for e < 4096
                 const double x[3] = {pts_c[0][c], pts_c[1][c], pts_c[2][c]};
                 const double y[3] = {pts_a[0][a], pts_a[1][a], pts_a[2][a]};
@@ -382,7 +388,7 @@ __global__ __launch_bounds__(256) void k_fill_N(int kernel, double ell, double s
             __syncthreads();
             if (!Np) continue;
             const float invp = 1.0f / (float)na;
-            for (int e = threadIdx.x; e < na * nc; e += 256) {
+            for (int e = threadIdx.x; e < na * nc; e += TH) {
                 const int c = (int)((e + 0.5f) * invp), a = e - c * na;
                 Np[(int64_t)(c0 + c) * lenp + a0 + a] = tile[c * (TA + 1) + a];
             }
@@ -390,12 +396,12 @@ __global__ __launch_bounds__(256) void k_fill_N(int kernel, double ell, double s
         }
     // padding
     if (len > ca)
-        for (int32_t a = threadIdx.x; a < ra; a += 256) {
+        for (int32_t a = threadIdx.x; a < ra; a += TH) {
             Nb[(int64_t)a * len + ca] = (TN)0;
             if (cplx) Nb[(int64_t)a * len + ca + n_plane] = (TN)0;
         }
     if (Np && lenp > ra)
-        for (int32_t c = threadIdx.x; c < ca; c += 256) Np[(int64_t)c * lenp + ra] = (TN)0;
+        for (int32_t c = threadIdx.x; c < ca; c += TH) Np[(int64_t)c * lenp + ra] = (TN)0;
 }
 
 // coupling matrices and near field, system by system (each with its own kernel
@@ -412,7 +418,8 @@ hipError_t fill_SN(const DevMat &dm, hipStream_t st) {
         const double npts = (double)(P.sys_row[i + 1] - P.sys_row[i]);  // points of system i
         // the exponential kernel in its own form per order
         auto fill_exp = [&](auto Pc) {
-            hipLaunchKernelGGL((k_fill_S_exp<T, decltype(Pc)::value>), dim3((unsigned)na), dim3(256), 0, st, ell,
+            constexpr int P1 = decltype(Pc)::value;
+            hipLaunchKernelGGL((k_fill_S_exp<T, P1>), dim3((unsigned)na), dim3(P1 <= 2 ? 64 : 256), 0, st, ell,
                                dm.adm_row, dm.adm_col, dm.nodes, (T *)dm.S, a, dm.adm_ptr,
                                P.sym_lists ? dm.adm_cptr : nullptr, dm.adm_cblk);
         };
@@ -431,11 +438,18 @@ hipError_t fill_SN(const DevMat &dm, hipStream_t st) {
             hipLaunchKernelGGL(k_fill_S<T>, dim3((unsigned)na), dim3(256), 0, st, dm.k, kernel, ell, npts,
                                dm.adm_row + a, dm.adm_col + a, dm.nodes, (T *)dm.S + a * dm.s_blk, dm.swz, dm.s_blk,
                                dm.s_plane);
-        if (nq > 0)
-            hipLaunchKernelGGL(k_fill_N<TN>, dim3((unsigned)nq), dim3(256), 0, st, kernel, ell, shift, npts, q,
-                               dm.near_row, dm.near_col, dm.near_off, dm.first, dm.size, dm.pts, (TN *)dm.N,
+        auto fill_near = [&](auto TAc) {
+            constexpr int TA = decltype(TAc)::value;
+            hipLaunchKernelGGL((k_fill_N<TN, TA>), dim3((unsigned)nq), dim3(TA > 16 ? 256 : 64), 0, st, kernel, ell, shift,
+                               npts, q, dm.near_row, dm.near_col, dm.near_off, dm.first, dm.size, dm.pts, (TN *)dm.N,
                                dm.near_t, dm.n_plane, dm.leaf_of, dm.near_ptr, P.sym_lists ? dm.near_cptr : nullptr,
                                dm.near_cblk);
+        };
+        if (nq > 0) {
+            if (dm.max_leaf <= 16) fill_near(std::integral_constant<int, 16>{});
+            else if (dm.max_leaf <= 32) fill_near(std::integral_constant<int, 32>{});
+            else fill_near(std::integral_constant<int, 64>{});
+        }
     }
     return hipGetLastError();
 }
