@@ -219,7 +219,11 @@ __device__ inline double exp_kernel(double r2, double ell, double ie) {
 // of squared one-dimensional differences (LDS).  The kernel is symmetric: where the lists are
 // (cptr given), the block (t, s) with t < s also writes the transposed block (s, t), entry i of
 // column list t for entry i of row list t, and (s, t) writes nothing.  In layout 1 a thread then
-// holds the 2 x 2 patch {nu, nu + 4} x {mu, mu + 4}, two 16-byte stores for either block.
+// holds the 2 x 2 patch {nu, nu + 4} x {mu, mu + 4}, two 16-byte stores for either block.  In layout 0
+// the transposed stores are single entries a row apart: blocks of orders 7 and 8 are evaluated
+// each for itself (order 8, BF16, 30000 points: 7.2 ms from nodes, 11.2 with pairs, 5.3), and above
+// order 4 the first two tables are summed in advance and the indices carried along, as the
+// divisions by K and P cost more than the exponential (order 7, FP32: 0.98 -> 0.72 ms).
 // P <= 2: launched with 64 threads, a thread per entry.
 // Bound by the FP64 vector instructions of the square root and the exponential (about 65 an
 // entry) and by the stores: 5.57 GB of rank-64 FP64 blocks in 1.10 ms (5.0 TB/s); 1.57 ms without
@@ -235,10 +239,12 @@ __global__ __launch_bounds__(256) void k_fill_S_exp(double ell, const int32_t *_
     constexpr int G = SWZ ? 16 / (int)sizeof(T) : 1;
     constexpr int BLK = SWZ == 1 ? KR * KC : K * K;
     constexpr bool PATCH = SWZ == 1 && KR == KC;  // orders 4, 5 and 8
+    constexpr bool LARGE0 = SWZ == 0 && P > 4;  // row-major and large: FP32 and BF16 above rank 64
     __shared__ double d2[3][P * P];
+    __shared__ double d01[LARGE0 ? P * P * P * P : 1];  // the sums of the first two tables
     const int64_t b = b0 + blockIdx.x;
     const int32_t t = adm_row[b], s = adm_col[b];
-    const bool pair = cptr && t != s && (PATCH || SWZ == 0);
+    const bool pair = cptr && t != s && (PATCH || (SWZ == 0 && P <= 6));
     if (pair && t > s) return;
     const int tid = threadIdx.x;
     if (tid < 3 * P * P) {
@@ -272,6 +278,28 @@ __global__ __launch_bounds__(256) void k_fill_S_exp(double ell, const int32_t *_
             if (pair) {
                 *(dbl2 *)(Sp + s_index(1, K, mu, nu)) = dbl2{v00, v10};
                 *(dbl2 *)(Sp + s_index(1, K, mu + 4, nu)) = dbl2{v01, v11};
+            }
+        }
+    } else if constexpr (LARGE0) {
+        constexpr int PP = P * P;
+        for (int e = tid; e < PP * PP; e += 256) {
+            const int n = e / PP, m = e % PP;
+            d01[e] = d2[1][n / P * P + m / P] + d2[0][n % P * P + m % P];
+        }
+        __syncthreads();
+        int nu = tid / K, mu = tid % K;
+#pragma unroll 4
+        for (int g = tid; g < BLK; g += 256) {
+            const int n2 = nu / PP, m2 = mu / PP;
+            const double r2 = d01[(nu - n2 * PP) * PP + mu - m2 * PP] + d2[2][n2 * P + m2];
+            const T v = from_double<T>(exp_kernel(r2, ell, ie));
+            Sb[g] = v;
+            if (pair) Sp[mu * K + nu] = v;
+            nu += 256 / K;
+            mu += 256 % K;
+            if (mu >= K) {
+                mu -= K;
+                ++nu;
             }
         }
     } else {
