@@ -398,9 +398,9 @@ typedef struct {
     int32_t fuse_up;   /* forward leaf and upward pass in one launch: 1 on; 0 (built-in
                           rule) and 2 level by level                                   */
     int32_t leaf_kind; /* leaf stage (32 * np_leaf columns per wave): 0 built-in rule
-                          (3 where its table of near rows fits in LDS and the operator
-                          is real, else 1); 1 a work-group per leaf, each wave a 64-row
-                          tile of its share of the terms; 2 a wave per 32-row band of a
+                          (3 where its table of near rows fits in LDS, else 1); 1 a
+                          work-group per leaf, each wave a 64-row tile of its share of
+                          the terms; 2 a wave per 32-row band of a
                           leaf, every term in turn (FP64 only; 1 for FP32 / BF16); 3 a
                           work-group per leaf, the near blocks and the basis as one
                           contraction in rounds of 16 rows, 16-row tiles of the leaf

@@ -1,4 +1,4 @@
-// Differentiation of the H^2 product (FP64 operators).
+// Differentiation of the H^2 product (FP64 operators of rank up to 64).
 //
 // Adjoint product Y = beta Y + alpha A^T X: the forward transformation of X,
 // then for every column cluster s its column list (every admissible block
@@ -24,259 +24,6 @@
 namespace h2x {
 
 namespace {
-
-constexpr int TR = 64;  // tile of the transposed coupling / near kernels
-constexpr int TC = 32;
-
-__device__ inline double dg_dell(int kernel, double ell, const double *a, const double *b) {
-    if (kernel != H2X_KERNEL_EXP) return 0.0;
-    const double dx = a[0] - b[0], dy = a[1] - b[1], dz = a[2] - b[2];
-    const double r = sqrt(dx * dx + dy * dy + dz * dz);
-    return (r / (ell * ell)) * exp(-r / ell);
-}
-
-__device__ inline void tile_fma(double acc[8], const double (*As)[TR + 1], const double (*Bs)[TC], int kc, int rg,
-                                int j) {
-    for (int c = 0; c < kc; ++c) {
-        const double b = Bs[c][j];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) acc[q] += As[rg + 8 * q][c] * b;
-    }
-}
-
-// y_s = sum over the column list of s of S_b^T x_{t(b)}  (every cluster s)
-__global__ __launch_bounds__(256) void k_coupling_adj(int k, int64_t m, const int64_t *__restrict__ cptr,
-                                                      const int64_t *__restrict__ cblk,
-                                                      const int32_t *__restrict__ adm_row,
-                                                      const double *__restrict__ S, int swz,
-                                                      const double *__restrict__ xh, double *__restrict__ yh,
-                                                      int64_t ldh) {
-    __shared__ double As[TR][TR + 1];
-    __shared__ double Bs[TR][TC];
-    const int32_t s = blockIdx.x;
-    const int64_t j0 = (int64_t)blockIdx.y * TC;
-    const int mc = (int)min<int64_t>(TC, m - j0);
-    const int tid = threadIdx.x, rg = tid >> 5, j = tid & 31;
-    for (int n0 = 0; n0 < k; n0 += TR) {
-        double acc[8] = {};
-        for (int64_t q = cptr[s]; q < cptr[s + 1]; ++q) {
-            const int64_t b = cblk[q];
-            const int32_t t = adm_row[b];
-            const double *Sb = S + b * s_block(swz, k);
-            for (int u0 = 0; u0 < k; u0 += TR) {
-                const int uc = min(TR, k - u0);
-                // As[mu][nu] = S_b[nu][mu]
-                for (int e = tid; e < TR * TR; e += 256) {
-                    const int mu = e / TR, nu = e % TR;
-                    As[mu][nu] = (nu < uc && n0 + mu < k) ? Sb[s_index(swz, k, u0 + nu, n0 + mu)] : 0.0;
-                }
-                for (int e = tid; e < TR * TC; e += 256) {
-                    const int nu = e / TC, jj = e % TC;
-                    Bs[nu][jj] = (nu < uc && jj < mc) ? xh[((int64_t)t * k + u0 + nu) * ldh + j0 + jj] : 0.0;
-                }
-                __syncthreads();
-                tile_fma(acc, As, Bs, uc, rg, j);
-                __syncthreads();
-            }
-        }
-        if (j < mc)
-            for (int q = 0; q < 8; ++q) {
-                const int mu = n0 + rg + 8 * q;
-                if (mu < k) yh[((int64_t)s * k + mu) * ldh + j0 + j] = acc[q];
-            }
-    }
-}
-
-// Y|_s = beta Y|_s + alpha (V_s y_s + sum over the near column list of s of N_ts^T X|_t)
-__global__ __launch_bounds__(256) void k_leaf_near_adj(int k, int64_t m, const int32_t *__restrict__ leaves,
-                                                       const int32_t *__restrict__ first,
-                                                       const int32_t *__restrict__ size,
-                                                       const int64_t *__restrict__ perm, const double *__restrict__ V,
-                                                       const double *__restrict__ yh, int64_t ldh,
-                                                       const int64_t *__restrict__ ncptr,
-                                                       const int64_t *__restrict__ ncblk,
-                                                       const int32_t *__restrict__ near_row,
-                                                       const int64_t *__restrict__ near_off, int near_t,
-                                                       const double *__restrict__ N, const double *__restrict__ X,
-                                                       int64_t ldx, double alpha, double beta,
-                                                       double *__restrict__ Y, int64_t ldy) {
-    __shared__ double As[TR][TR + 1];
-    __shared__ double Bs[TR][TC];
-    const int32_t l = blockIdx.x;
-    const int32_t s = leaves[l];
-    const int64_t j0 = (int64_t)blockIdx.y * TC;
-    const int mc = (int)min<int64_t>(TC, m - j0);
-    const int tid = threadIdx.x, rg = tid >> 5, j = tid & 31;
-    const int64_t r0 = first[s];
-    const int ns = size[s];
-    for (int c0 = 0; c0 < ns; c0 += TR) {
-        const int cc = min(TR, ns - c0);
-        double acc[8] = {};
-        for (int u0 = 0; u0 < k; u0 += TR) {
-            const int uc = min(TR, k - u0);
-            for (int e = tid; e < TR * TR; e += 256) {
-                const int c = e / TR, nu = e % TR;
-                As[c][nu] = (c < cc && nu < uc) ? V[(r0 + c0 + c) * k + u0 + nu] : 0.0;
-            }
-            for (int e = tid; e < TR * TC; e += 256) {
-                const int nu = e / TC, jj = e % TC;
-                Bs[nu][jj] = (nu < uc && jj < mc) ? yh[((int64_t)s * k + u0 + nu) * ldh + j0 + jj] : 0.0;
-            }
-            __syncthreads();
-            tile_fma(acc, As, Bs, uc, rg, j);
-            __syncthreads();
-        }
-        for (int64_t q = ncptr[l]; q < ncptr[l + 1]; ++q) {
-            const int64_t b = ncblk[q];
-            const int32_t t = near_row[b];
-            const int nt = size[t];
-            const int64_t nt2 = pad_rows(nt), ft = first[t];
-            const double *Nb = N + near_off[b];
-            for (int i0 = 0; i0 < nt; i0 += TR) {
-                const int ic = min(TR, nt - i0);
-                // As[c][i] = N_ts[i][c]
-                for (int e = tid; e < TR * TR; e += 256) {
-                    const int c = e / TR, i = e % TR;
-                    double v = 0.0;
-                    if (c < cc && i < ic) {
-                        const int64_t o = near_t ? (int64_t)(c0 + c) * nt2 + i0 + i : (int64_t)(i0 + i) * ns + c0 + c;
-                        v = Nb[o];
-                    }
-                    As[c][i] = v;
-                }
-                for (int e = tid; e < TR * TC; e += 256) {
-                    const int i = e / TC, jj = e % TC;
-                    Bs[i][jj] = (i < ic && jj < mc) ? X[perm[ft + i0 + i] * ldx + j0 + jj] : 0.0;
-                }
-                __syncthreads();
-                tile_fma(acc, As, Bs, ic, rg, j);
-                __syncthreads();
-            }
-        }
-        if (j < mc)
-            for (int q = 0; q < 8; ++q) {
-                const int c = rg + 8 * q;
-                if (c < cc) {
-                    double *y = &Y[perm[r0 + c0 + c] * ldy + j0 + j];
-                    const double v = alpha * acc[q];
-                    *y = (beta == 0.0) ? v : beta * *y + v;
-                }
-            }
-    }
-}
-
-// one admissible block per work-group: D = scale * dyhat_t xhat_s^T (k x k, k <= 64);
-// dS_b = D if requested; part[b] = sum of (dg/dell) * D in a fixed order (0 unless want_dell)
-__global__ __launch_bounds__(256) void k_grad_S(int k, int64_t m, const int32_t *__restrict__ adm_row,
-                                                const int32_t *__restrict__ adm_col,
-                                                const double *__restrict__ nodes, int kernel, double ell,
-                                                const double *__restrict__ dh, const double *__restrict__ xh,
-                                                int64_t ldh, double scale, int want_dell, double *__restrict__ dS,
-                                                double *__restrict__ part) {
-    __shared__ double sd[64][65], sx[64][65];
-    __shared__ double red[256];
-    const int64_t b = blockIdx.x;
-    const int32_t t = adm_row[b], s = adm_col[b];
-    const int tid = threadIdx.x, kk = k * k;
-    double acc[16] = {};
-    for (int64_t j0 = 0; j0 < m; j0 += 64) {
-        const int mc = (int)min<int64_t>(64, m - j0);
-        for (int e = tid; e < k * 64; e += 256) {
-            const int nu = e / 64, jj = e % 64;
-            sd[nu][jj] = jj < mc ? dh[((int64_t)t * k + nu) * ldh + j0 + jj] : 0.0;
-            sx[nu][jj] = jj < mc ? xh[((int64_t)s * k + nu) * ldh + j0 + jj] : 0.0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int e = tid + 256 * u;
-            if (e < kk) {
-                const int nu = e / k, mu = e % k;
-                double a = acc[u];
-                for (int jj = 0; jj < mc; ++jj) a += sd[nu][jj] * sx[mu][jj];
-                acc[u] = a;
-            }
-        }
-        __syncthreads();
-    }
-    double g = 0.0;
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        const int e = tid + 256 * u;
-        if (e < kk) {
-            const int nu = e / k, mu = e % k;
-            const double d = scale * acc[u];
-            if (dS) dS[b * kk + e] = d;
-            if (want_dell)
-                g += dg_dell(kernel, ell, &nodes[((int64_t)t * k + nu) * 3], &nodes[((int64_t)s * k + mu) * 3]) * d;
-        }
-    }
-    red[tid] = g;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (tid < w) red[tid] += red[tid + w];
-        __syncthreads();
-    }
-    if (tid == 0) part[b] = red[0];
-}
-
-// one near-field block per work-group: D = scale * dY|_t X|_s^T (tree-ordered dY, X);
-// dN_b = D (row-major |t| x |s|) if requested; part[q] = sum of (dg/dell) * D (0 unless want_dell)
-__global__ __launch_bounds__(256) void k_grad_N(int64_t m, const int32_t *__restrict__ near_row,
-                                                const int32_t *__restrict__ near_col,
-                                                const int64_t *__restrict__ near_off_rm,
-                                                const int32_t *__restrict__ first, const int32_t *__restrict__ size,
-                                                const double *__restrict__ pts, int kernel, double ell,
-                                                const double *__restrict__ dYt, const double *__restrict__ Xt,
-                                                int64_t ldt, double scale, int want_dell, double *__restrict__ dN,
-                                                double *__restrict__ part) {
-    __shared__ double sd[64][33], sx[64][33];
-    __shared__ double red[256];
-    const int64_t q = blockIdx.x;
-    const int32_t t = near_row[q], s = near_col[q];
-    const int nt = size[t], ns = size[s];
-    const int64_t ft = first[t], fs = first[s];
-    const int tid = threadIdx.x;
-    double g = 0.0;
-    for (int i0 = 0; i0 < nt; i0 += 64)
-        for (int c0 = 0; c0 < ns; c0 += 64) {
-            const int ic = min(64, nt - i0), cc = min(64, ns - c0);
-            double acc[16] = {};
-            for (int64_t j0 = 0; j0 < m; j0 += 32) {
-                const int mc = (int)min<int64_t>(32, m - j0);
-                for (int e = tid; e < 64 * 32; e += 256) {
-                    const int r = e / 32, jj = e % 32;
-                    sd[r][jj] = (r < ic && jj < mc) ? dYt[(ft + i0 + r) * ldt + j0 + jj] : 0.0;
-                    sx[r][jj] = (r < cc && jj < mc) ? Xt[(fs + c0 + r) * ldt + j0 + jj] : 0.0;
-                }
-                __syncthreads();
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int e = tid + 256 * u, i = e / 64, c = e % 64;
-                    double a = acc[u];
-                    for (int jj = 0; jj < mc; ++jj) a += sd[i][jj] * sx[c][jj];
-                    acc[u] = a;
-                }
-                __syncthreads();
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int e = tid + 256 * u, i = e / 64, c = e % 64;
-                if (i < ic && c < cc) {
-                    const double d = scale * acc[u];
-                    if (dN) dN[near_off_rm[q] + (int64_t)(i0 + i) * ns + c0 + c] = d;
-                    if (want_dell) g += dg_dell(kernel, ell, &pts[3 * (ft + i0 + i)], &pts[3 * (fs + c0 + c)]) * d;
-                }
-            }
-        }
-    red[tid] = g;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (tid < w) red[tid] += red[tid + w];
-        __syncthreads();
-    }
-    if (tid == 0) part[q] = red[0];
-}
 
 // dell = sum of the per-block partial sums, in a fixed order: work-group g adds
 // entries [g * chunk, (g + 1) * chunk) into out[g] (one work-group: the total)
@@ -397,39 +144,28 @@ hipError_t run_matmul_adjoint(const DevMat &dm, int64_t m, double alpha, const d
     double *xh = (double *)ws, *yh = (double *)(ws + hat), *xt = (double *)(ws + 2 * hat);
     hipError_t e = run_forward_transform(dm, m, X, ldx, false, xh, ldh, xt, st);
     if (e != hipSuccess) return e;
-    if (dm.mc) {
-        // matrix-core path: the forward transformation left X in tree order in xt (leading dimension ldh)
-        const int nj = (int)std::min<int64_t>(4, (m + 15) / 16);
-        const unsigned gy = (unsigned)((m + 16 * nj - 1) / (16 * nj));
-        auto go = [&](auto NJc) {
-            constexpr int NJ = decltype(NJc)::value;
-            hipLaunchKernelGGL(adj::k_coupling_adj_mfma<NJ>, dim3(8 * ((dm.C + 7) / 8), gy), dim3(256), 0, st, dm.k,
-                               dm.swz, m, dm.C, dm.adm_cptr, dm.adm_cblk, dm.adm_row, (const double *)dm.S,
-                               (const double *)xh, yh, ldh);
-            hipError_t ee = run_down_pass(dm, m, yh, ldh, st);
-            if (ee != hipSuccess) return ee;
-            hipLaunchKernelGGL(adj::k_leaf_adj_mfma<NJ>, dim3(8 * ((dm.L + 7) / 8), gy), dim3(256), 0, st, dm.k, m,
-                               dm.L, dm.leaves, dm.first, dm.size, dm.perm, (const double *)dm.V,
-                               (const double *)yh, ldh, dm.near_cptr, dm.near_cblk, dm.near_row, dm.near_off,
-                               (const double *)dm.N, (const double *)xt, ldh, alpha, beta, Y, ldy);
-            return hipGetLastError();
-        };
-        switch (nj) {
-            case 1: return go(std::integral_constant<int, 1>{});
-            case 2: return go(std::integral_constant<int, 2>{});
-            case 3: return go(std::integral_constant<int, 3>{});
-            default: return go(std::integral_constant<int, 4>{});
-        }
+    // the forward transformation left X in tree order in xt (leading dimension ldh)
+    const int nj = (int)std::min<int64_t>(4, (m + 15) / 16);
+    const unsigned gy = (unsigned)((m + 16 * nj - 1) / (16 * nj));
+    auto go = [&](auto NJc) {
+        constexpr int NJ = decltype(NJc)::value;
+        hipLaunchKernelGGL(adj::k_coupling_adj_mfma<NJ>, dim3(8 * ((dm.C + 7) / 8), gy), dim3(256), 0, st, dm.k, dm.swz,
+                           m, dm.C, dm.adm_cptr, dm.adm_cblk, dm.adm_row, (const double *)dm.S, (const double *)xh, yh,
+                           ldh);
+        hipError_t ee = run_down_pass(dm, m, yh, ldh, st);
+        if (ee != hipSuccess) return ee;
+        hipLaunchKernelGGL(adj::k_leaf_adj_mfma<NJ>, dim3(8 * ((dm.L + 7) / 8), gy), dim3(256), 0, st, dm.k, m, dm.L,
+                           dm.leaves, dm.first, dm.size, dm.perm, (const double *)dm.V, (const double *)yh, ldh,
+                           dm.near_cptr, dm.near_cblk, dm.near_row, dm.near_off, (const double *)dm.N,
+                           (const double *)xt, ldh, alpha, beta, Y, ldy);
+        return hipGetLastError();
+    };
+    switch (nj) {
+        case 1: return go(std::integral_constant<int, 1>{});
+        case 2: return go(std::integral_constant<int, 2>{});
+        case 3: return go(std::integral_constant<int, 3>{});
+        default: return go(std::integral_constant<int, 4>{});
     }
-    const unsigned gy = (unsigned)((m + TC - 1) / TC);
-    hipLaunchKernelGGL(k_coupling_adj, dim3(dm.C, gy), dim3(256), 0, st, dm.k, m, dm.adm_cptr, dm.adm_cblk,
-                       dm.adm_row, (const double *)dm.S, dm.swz, (const double *)xh, yh, ldh);
-    e = run_down_pass(dm, m, yh, ldh, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_leaf_near_adj, dim3(dm.L, gy), dim3(256), 0, st, dm.k, m, dm.leaves, dm.first, dm.size,
-                       dm.perm, (const double *)dm.V, (const double *)yh, ldh, dm.near_cptr, dm.near_cblk,
-                       dm.near_row, dm.near_off, dm.near_t, (const double *)dm.N, X, ldx, alpha, beta, Y, ldy);
-    return hipGetLastError();
 }
 
 __global__ void k_fill0(int64_t count, double *__restrict__ p) {
@@ -519,20 +255,15 @@ hipError_t run_grad(const DevMat &dm, int64_t m, const double *X, int64_t ldx, c
         if (e == hipSuccess) e = run_forward_transform(dm, m, dY, lddy, false, w.dh, ldh, w.xt_ws, st);
         if (e != hipSuccess) return e;
         if (dm.n_adm > 0) {
-            if (dm.mc) {
-                // LDS tiles sized to the column chunk (16, 32 or 64 columns)
-                auto go = [&](auto CWc) {
-                    hipLaunchKernelGGL(adj::k_grad_S_mfma<decltype(CWc)::value>, dim3((unsigned)dm.n_adm), dim3(256), 0,
-                                       st, dm.k, m, dm.adm_row, dm.adm_col, dm.nodes, dm.kernel, dm.ell,
-                                       (const double *)w.dh, (const double *)w.xh, ldh, scale, cpl_b, dS, w.part);
-                };
-                if (m <= 16) go(std::integral_constant<int, 16>{});
-                else if (m <= 32) go(std::integral_constant<int, 32>{});
-                else go(std::integral_constant<int, 64>{});
-            } else
-                hipLaunchKernelGGL(k_grad_S, dim3((unsigned)dm.n_adm), dim3(256), 0, st, dm.k, m, dm.adm_row,
-                                   dm.adm_col, dm.nodes, dm.kernel, dm.ell, (const double *)w.dh,
+            // LDS tiles sized to the column chunk (16, 32 or 64 columns)
+            auto go = [&](auto CWc) {
+                hipLaunchKernelGGL(adj::k_grad_S_mfma<decltype(CWc)::value>, dim3((unsigned)dm.n_adm), dim3(256), 0, st,
+                                   dm.k, m, dm.adm_row, dm.adm_col, dm.nodes, dm.kernel, dm.ell, (const double *)w.dh,
                                    (const double *)w.xh, ldh, scale, cpl_b, dS, w.part);
+            };
+            if (m <= 16) go(std::integral_constant<int, 16>{});
+            else if (m <= 32) go(std::integral_constant<int, 32>{});
+            else go(std::integral_constant<int, 64>{});
         }
     }
     if (dN || nr_b) {
@@ -542,21 +273,15 @@ hipError_t run_grad(const DevMat &dm, int64_t m, const double *X, int64_t ldx, c
         hipLaunchKernelGGL(k_gather_even, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, dm.n, m, dm.perm, dY,
                            lddy, w.dYt, ldh);
         if (dm.n_near > 0) {
-            if (dm.mc) {
-                auto go = [&](auto CWc) {
-                    hipLaunchKernelGGL(adj::k_grad_N_mfma<decltype(CWc)::value>, dim3((unsigned)dm.n_near), dim3(256), 0,
-                                       st, m, dm.near_row, dm.near_col, dm.near_off_rm, dm.first, dm.size, dm.pts,
-                                       dm.kernel, dm.ell, (const double *)w.dYt, (const double *)w.Xt, ldh, scale, nr_b,
-                                       dN, w.part + dm.n_adm);
-                };
-                if (m <= 16) go(std::integral_constant<int, 16>{});
-                else if (m <= 32) go(std::integral_constant<int, 32>{});
-                else go(std::integral_constant<int, 64>{});
-            } else
-                hipLaunchKernelGGL(k_grad_N, dim3((unsigned)dm.n_near), dim3(256), 0, st, m, dm.near_row,
-                                   dm.near_col, dm.near_off_rm, dm.first, dm.size, dm.pts, dm.kernel, dm.ell,
-                                   (const double *)w.dYt, (const double *)w.Xt, ldh, scale, nr_b, dN,
+            auto go = [&](auto CWc) {
+                hipLaunchKernelGGL(adj::k_grad_N_mfma<decltype(CWc)::value>, dim3((unsigned)dm.n_near), dim3(256), 0, st,
+                                   m, dm.near_row, dm.near_col, dm.near_off_rm, dm.first, dm.size, dm.pts, dm.kernel,
+                                   dm.ell, (const double *)w.dYt, (const double *)w.Xt, ldh, scale, nr_b, dN,
                                    w.part + dm.n_adm);
+            };
+            if (m <= 16) go(std::integral_constant<int, 16>{});
+            else if (m <= 32) go(std::integral_constant<int, 32>{});
+            else go(std::integral_constant<int, 64>{});
         }
     }
     if (fused) return run_dell_fused(dm, ds, m, X, ldx, dY, lddy, dell, scale, cpl, nr, w, st);

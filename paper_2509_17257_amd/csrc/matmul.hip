@@ -45,8 +45,6 @@ __global__ void k_pack_bf16(int64_t cnt4, const float4 *__restrict__ x, uint2 *_
                        (uint32_t)bf16_bits(v.z) | ((uint32_t)bf16_bits(v.w) << 16)};
     }
 }
-// forward leaf transform for k <= 32 with V_t^T straight into the matrix-core registers
-constexpr bool kSmallFwdLeaf = true;
 
 template <typename T, typename Acc>
 __device__ inline Acc ld_op(const T *p) { return (Acc)to_double(*p); }
@@ -363,12 +361,9 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
         if (t64)
             hipLaunchKernelGGL(mfma::k_fwd_leaf64<NJ>, dim3(dm.L, gy), dim3(256), 0, st, m, dm.leaves, dm.first,
                                dm.size, V, Xt, ldxt, xh, ldh, sk);
-        else if (kSmallFwdLeaf)
+        else
             hipLaunchKernelGGL(mfma::k_fwd_leaf_small<NJ>, dim3(dm.L, gy), dim3(128), 0, st, dm.k, m, dm.leaves,
                                dm.first, dm.size, V, Xt, ldxt, xh, ldh, sk);
-        else
-            hipLaunchKernelGGL(mfma::k_fwd_leaf<NJ>, dim3(dm.L, gy), dim3(256), 0, st, dm.k, m, dm.leaves, dm.first,
-                               dm.size, dm.perm, V, Xt, ldxt, 1, xh, ldh, sk);
     };
     const unsigned gl = (unsigned)((m + 32 * NP - 1) / (32 * NP));
     // leaf stage: one contraction per leaf (built-in where its LDS table of near rows fits),
@@ -501,9 +496,9 @@ void matmul_mfma_f64(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
     };
     // complex operator: y-hat += S_im (J x-hat), so that y-hat = (S_re + i S_im) x-hat per complex column
     auto coupling = [&](hipStream_t s, int32_t nrows, const int32_t *rows, size_t keep) {
-        launch_coupling_fast(dm, m, xh, yh, ldh, s, sk, cfg.nj_coupling, 0, nrows, rows, keep);
+        launch_coupling(dm, m, xh, yh, ldh, s, sk, cfg.nj_coupling, 0, nrows, rows, keep);
         if (dm.cplx)
-            launch_coupling_fast(dm, m, xh, yh, ldh, s, sk, cfg.nj_coupling, 1, nrows, rows, keep);
+            launch_coupling(dm, m, xh, yh, ldh, s, sk, cfg.nj_coupling, 1, nrows, rows, keep);
     };
     const int dlo = std::max(1, P.adm_depth + 1);
     if (halves) {

@@ -1,5 +1,5 @@
-// Matrix-core (MFMA) coupling kernels for the FP64 operator (k = 64 below; a
-// small-rank variant for k <= 32 further down):
+// Matrix-core (MFMA) coupling kernel for the FP64 operator of rank 64 (smaller ranks in
+// coupling_small.hpp, larger ones and few rows in coupling_rows.hpp):
 //   y_t = sum_{(t,s) in C_t, admissible} S_b x_s     for every row cluster t.
 //
 // One work-group (4 waves) owns one row cluster t and a slab of up to 64
@@ -226,16 +226,14 @@ __global__ __launch_bounds__(256) void k_coupling_mfma_f64(int64_t m, int32_t C,
     coupling64<NJ>(t, j0, (int)min<int64_t>(MC, m - j0), adm_ptr, adm_col, S, xh, yh, ldh, jpass, xs);
 }
 
-// Launches the matrix-core coupling stage when the operator's layout supports
-// it; returns false (launching nothing) otherwise.
-inline bool launch_coupling_fast(const DevMat &dm, int64_t m, const double *xh, double *yh, int64_t ldh, hipStream_t st,
-                          Skip skip, int nj_force, int jpass = 0, int32_t nrows = -1, const int32_t *rows = nullptr,
-                          size_t keep_lds = 0) {
-    if (!dm.mc || !dm.cpl_order) return false;
+// The coupling stage of the ranks up to 64 (dm.mc).
+inline void launch_coupling(const DevMat &dm, int64_t m, const double *xh, double *yh, int64_t ldh, hipStream_t st,
+                            Skip skip, int nj_force, int jpass = 0, int32_t nrows = -1, const int32_t *rows = nullptr,
+                            size_t keep_lds = 0) {
     // all rows in cpl_order, or the part (nrows, rows) of them
     const int32_t C = rows ? nrows : dm.C;
     const int32_t *order = rows ? rows : dm.cpl_order;
-    if (C <= 0) return true;
+    if (C <= 0) return;
     // column tiles per work-group: as many as the columns fill, fewer where the rows alone do not
     // fill the chip (rank 64, sphere: 375 rows, 64 columns: 4 tiles 151, 2 tiles 116 us; 745 rows:
     // 198 and 214 us; 32 columns, 193 rows: 82 and 67 us); the bits do not depend on it
@@ -251,12 +249,11 @@ inline bool launch_coupling_fast(const DevMat &dm, int64_t m, const double *xh, 
     const double *S = (const double *)dm.S + (jpass ? dm.s_plane : 0);
     if (dm.k <= 32) {
         launch_coupling_small(dm, m, S, xh, yh, ldh, st, skip, nj_force, C, order, jpass);
-        return true;
+        return;
     }
-    if (dm.swz != 1 || dm.k != kMfmaK) return false;
     if (!nj_force && !keep_lds && coupling_in_tiles(dm.k, m, C)) {
         launch_coupling_tile(dm, m, S, xh, yh, ldh, st, skip, C, order, jpass);
-        return true;
+        return;
     }
     // keep_lds > 0: each work-group also takes unused dynamic LDS, so that a CU holds at
     // most two of them and keep_lds bytes stay free for a work-group of another launch
@@ -294,7 +291,6 @@ inline bool launch_coupling_fast(const DevMat &dm, int64_t m, const double *xh, 
             else go(four, one);
         }
     }
-    return true;
 }
 
 }  // namespace h2x

@@ -269,8 +269,8 @@ static __global__ void k_zero_i32(int64_t count, int32_t *__restrict__ p) {
 // shared by four k-steps through the L1), so that only the right operand (x-hat or y-hat
 // rows, 64 x 16*NJ) goes through LDS, both upward terms at once behind one barrier.  The
 // k-steps and terms are summed in ascending order.
-//   upward:   x_t = E_{s0}^T x_{s0} + E_{s1}^T x_{s1}   (list, son as for k_up)
-//   downward: y_c += E_c y_{par(c)}                    (list, par as for k_down)
+//   upward:   x_t = E_{s0}^T x_{s0} + E_{s1}^T x_{s1}   (son: two sons per entry of list)
+//   downward: y_c += E_c y_{par(c)}                    (par: the father of each entry of list)
 // by: the column slab; bs: NT x 64 x (16 NJ + 1) doubles of LDS
 template <int NJ, int NT, int TR>
 __device__ inline void transfer_rows(const double *const *Ea, const int64_t *brow, int64_t m,
