@@ -16,12 +16,13 @@
 // tiles and an even NC, two column halves (each loads one operand for itself), so that few leaves
 // still fill the chip.  The sums are the same bit for bit.  Bound by the FP32 matrix cores and the
 // loads that feed them.  Slabs of 32 or 64 columns spent up to a quarter of the products on padding
-// and row groups 22 GB of cache traffic where 13 do: 45 columns, n = 99991, BF16 basis, leaf stage 1029 -> 790 us; 64 columns,
-// n = 262144, FP32 2330 -> 2150 us.  Above four tiles per wave the registers allow two waves per
-// SIMD and one round of loads ahead (two rounds ahead spill: 5 x slower, half rounds three ahead are
-// 1 % slower); up to four tiles of a chunk above 32 rows two rounds fly (leaves of up to 100 points, 32
-// columns, BF16: leaf stage 335 -> 315 us).  The row table and the partial tiles take the same LDS (beside each other: + 8 % of a product with
-// tables of 30 KB).
+// and row groups 22 GB of cache traffic where 13 do: 45 columns, n = 99991, BF16 basis, leaf stage
+// 1029 -> 790 us; 64 columns, n = 262144, FP32 2330 -> 2150 us.  Above four tiles per wave the
+// registers allow two waves per SIMD and one round of loads ahead (two rounds ahead spill: 5 x
+// slower, half rounds three ahead are 1 % slower); up to four tiles of a chunk above 32 rows two
+// rounds fly (leaves of up to 100 points, 32 columns, BF16: leaf stage 335 -> 315 us).  The row
+// table and the partial tiles take the same LDS (beside each other: + 8 % of a product with tables
+// of 30 KB).
 //
 // Lane layout of v_mfma_f32_16x16x4f32 (A: 16 x 4, B: 4 x 16, D: 16 x 16): lane l holds
 // A[l % 16][l / 16], B[l / 16][l % 16] and D rows 4 (l / 16) + q, column l % 16 (q = 0..3).
