@@ -66,7 +66,7 @@ struct LeafCatLpArgs {
     double alpha, beta;
     double *Y;
     int64_t ldy;
-    int tree_order, round_y;
+    int tree_order;
     Skip skip;
 };
 
@@ -133,7 +133,7 @@ __device__ inline void leaf_cat_lp_chunk(const LeafCatLpArgs &a, int g, int lr, 
     };
     // the products of round r; rows past its segment are zeroed here
     auto multiply = [&](int r, const CatRoundLp<NC, NT> &R, flt4v(&ac)[NC][NT]) {
-        const bool basis = r >= RN, rnd = a.round_y && basis;
+        const bool basis = r >= RN;
         const int rem = basis ? k - 16 * (r - RN) : rn - 16 * r;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -142,7 +142,9 @@ __device__ inline void leaf_cat_lp_chunk(const LeafCatLpArgs &a, int g, int lr, 
             for (int J = 0; J < NC; ++J) {
                 float v = ((NC & 1) && J == NC - 1) ? R.c[u] : R.a[J >> 1][u][J & 1];
                 v = ok ? v : 0.f;
-                if (rnd) v = round_bf16(v);
+                // (not in the FP32 kernel: the branches of a rounding split a round's products up)
+                if constexpr (std::is_same<TV, bf16_t>::value)
+                    if (basis) v = round_bf16(v);
 #pragma unroll
                 for (int I = 0; I < NT; ++I)
                     ac[J][I] = __builtin_amdgcn_mfma_f32_16x16x4f32(
@@ -211,6 +213,10 @@ __device__ inline void leaf_cat_lp_chunk(const LeafCatLpArgs &a, int g, int lr, 
 // one (leaf, column slab) per work-group, mapped to XCDs as in the FP64 form (slot & 7 is the
 // XCD, whose leaves form one contiguous eighth of the launch order; the slabs of one leaf are
 // consecutive slots of one XCD).  Dynamic LDS: the near-row table, then the partial tiles.
+// ROWS: the largest leaf, 32, 64 or 128 for any.  64: the lane's number is opaque in each chunk, as the
+// offsets of every form would else be held across the table's barriers (32 columns: 139 registers,
+// three waves per SIMD; 121, four; cube 60000, BF16 786 -> 772 us per product; larger leaves, two
+// chunks each, are faster without: sphere 79040, leaves of 80, FP32 526 / 536).
 template <int NC, int NW, int ROWS, typename TV>
 __global__ __launch_bounds__(64 * NW, 2) void k_leaf_cat_lp(LeafCatLpArgs a) {
     constexpr int MC = 16 * NC, LDR = MC + 1;
@@ -219,8 +225,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_leaf_cat_lp(LeafCatLpArgs a) {
     const int64_t slot = blockIdx.x;
     const int32_t per_xcd = (a.L + 7) / 8;
     const int nslab = (int)((a.m + MC - 1) / MC);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, lr = lane & 15,
-              lq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t qx = slot >> 3;
     const int32_t pos = (int32_t)((slot & 7) * per_xcd + qx / nslab);
     if (pos >= a.L) return;
@@ -241,6 +246,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_leaf_cat_lp(LeafCatLpArgs a) {
             nnear > 0 ? mfma::cat_build_rows(xrow, q0, nnear, nt2, a.near_col, a.near_off, a.first, a.size, threadIdx.x)
                       : 0;
         const int ic = min(64, nt - i0);
+        int lane = threadIdx.x & 63;
+        if (ROWS == 64) asm volatile("" : "+v"(lane));
+        const int lr = lane & 15, lq = lane >> 4;
         if (ic <= 16)
             leaf_cat_lp_chunk<NC, 1, 4, NW, LDR>(a, w, lr, lq, t, nb, vb, rn, nt2, i0, ic, j0, xc, xrow, red);
         else if (ROWS <= 32 || ic <= 32)

@@ -818,19 +818,25 @@ hipError_t matmul_lp(const DevMat &dm, const TuneCfg &cfg, int64_t m, double alp
         if (cat_ok && (cfg.leaf_kind == 0 || cfg.leaf_kind == 3)) {
             const lp::LeafCatLpArgs a{dm.k, m, dm.L, dm.leaf_order, dm.leaves, dm.first, dm.size, dm.perm,
                                       dm.Vt, dm.vt_off, yh, ldh, dm.near_ptr, dm.near_col, dm.near_off,
-                                      (const float *)dm.N, xt, ldxt, alpha, beta, Y, ldy, to, rb, sk};
+                                      (const float *)dm.N, xt, ldxt, alpha, beta, Y, ldy, to, sk};
             const unsigned grid = gl8 * (unsigned)((m + 16 * NC - 1) / (16 * NC));
-            const bool two = leaf_two_waves(grid, dm.max_leaf, cat_lds);
-            // leaves of up to 32 rows: the forms for more rows and their registers are left out
-            // (leaves of 16, 32 columns, FP32: 803 against 841 us per product)
+            const bool two = leaf_two_waves_lp(grid, NC, dm.max_leaf, cat_lds);
+            // leaves of up to 32 or 64 rows: kernels without the forms for more rows and their registers
+            // (leaves of 16, 32 columns, FP32: 803 against 841 us per product; cube 60000, leaves of 64,
+            // BF16 772 against 786)
             auto go = [&](auto n) {
                 constexpr int N = decltype(n)::value;
+                auto form = [&](auto kern, int threads) {
+                    hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), cat_lds, st, a);
+                };
                 if (two)
-                    hipLaunchKernelGGL((lp::k_leaf_cat_lp<N, 2, 64, T>), dim3(grid), dim3(128), cat_lds, st, a);
+                    form(&lp::k_leaf_cat_lp<N, 2, 128, T>, 128);
+                else if (dm.max_leaf > 64)
+                    form(&lp::k_leaf_cat_lp<N, 4, 128, T>, 256);
                 else if (dm.max_leaf > 32)
-                    hipLaunchKernelGGL((lp::k_leaf_cat_lp<N, 4, 64, T>), dim3(grid), dim3(256), cat_lds, st, a);
+                    form(&lp::k_leaf_cat_lp<N, 4, 64, T>, 256);
                 else
-                    hipLaunchKernelGGL((lp::k_leaf_cat_lp<N, 4, 32, T>), dim3(grid), dim3(256), cat_lds, st, a);
+                    form(&lp::k_leaf_cat_lp<N, 4, 32, T>, 256);
             };
             switch (NC) {
                 case 1: go(std::integral_constant<int, 1>{}); break;

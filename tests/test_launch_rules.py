@@ -16,6 +16,13 @@ int main() {
     if (leaf_two_waves(100000, 32, 1000)) return 3;  // at most two row tiles
     // a table of near rows that leaves room for three or two work-groups on a CU
     if (leaf_two_waves(100000, 64, 4 * 10730) || leaf_two_waves(100000, 100, 4 * 13905)) return 4;
+    // FP32 and BF16: one round of two-wave groups, or more than two and a half times the chip
+    using h2x::leaf_two_waves_lp;
+    if (!leaf_two_waves_lp(1280, 2, 64, 8000) || !leaf_two_waves_lp(1536, 1, 64, 16384)) return 5;
+    if (leaf_two_waves_lp(1279, 2, 64, 8000) || leaf_two_waves_lp(1537, 2, 64, 8000)) return 6;
+    if (leaf_two_waves_lp(1400, 2, 64, 16385) || leaf_two_waves_lp(1400, 2, 32, 8000) || leaf_two_waves_lp(1400, 2, 65, 8000)) return 7;
+    if (leaf_two_waves_lp(2559, 2, 64, 8000) || !leaf_two_waves_lp(2560, 2, 64, 8000)) return 8;
+    if (!leaf_two_waves_lp(2048, 3, 64, 8000) || leaf_two_waves_lp(1400, 3, 64, 8000)) return 9;
     return 0;
 }
 """
